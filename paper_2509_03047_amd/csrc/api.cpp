@@ -257,7 +257,9 @@ extern "C" int fr_verify_replicas_noalloc(const fr_plan* plan, const void* base_
   scr.flags = reinterpret_cast<uint32_t*>(p);
   scr.acc = reinterpret_cast<fr_chunk_sum*>(p + flag_bytes);
   scr.acc_b = reinterpret_cast<fr_chunk_sum*>(p + flag_bytes + acc_bytes);
-  return launch_result(launch_verify(plan->d_units, *walk, uint32_t(L.n_chunks), L.C, base_a,
+  SlotTable t = *walk;
+  t.parts = nullptr;  // accumulators per chunk: the array has no room for a place per slot
+  return launch_result(launch_verify(plan->d_units, t, uint32_t(L.n_chunks), L.C, base_a,
                                      base_b, diff_bitmap, n_diff, sums_a, sums_b, scr, plan->cfg,
                                      stream));
 }

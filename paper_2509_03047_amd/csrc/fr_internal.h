@@ -93,6 +93,19 @@ static_assert(sizeof(PlainUnit) == 32, "PlainUnit is 32 bytes");
 // (g mod 8) * stride + g / 8, so each XCD reads its own slots contiguously.
 constexpr uint32_t kSlotDerived = 0x80000000u;
 
+// Where the partial sums of one chunk lie: every workgroup of a whole-state
+// operation stores the sums of what it moved at its own place (XCD-major like
+// the slot it belongs to, so that no line of places is written by two XCDs),
+// and the finalize kernel folds a chunk's n places.
+constexpr uint32_t kPartB = 1;       // in the second array (unpack: parameter images)
+constexpr uint32_t kPartTile = 2;    // a tile walk's
+struct alignas(16) ChunkParts {
+  uint64_t first;  // first slot of the chunk; tiles: (unit << 32) | first tile
+  uint32_t n;      // slots (tiles)
+  uint32_t kind;   // kPart*; tiles: | (units its first tile holds before it, at most 2) << 8
+};
+static_assert(sizeof(ChunkParts) == 16, "ChunkParts is 16 bytes");
+
 struct SlotTable {
   const uint64_t* d = nullptr;  // NULL: implicit walk (below)
   uint64_t n = 0;       // slots (workgroups to launch)
@@ -119,6 +132,10 @@ struct SlotTable {
   // Implicit walk over a list built on the device: n covers the longest
   // list, and only the slots of the first *count units work.
   const uint64_t* count = nullptr;
+  // Per chunk id, where its partial sums lie (NULL: the operation adds into
+  // per-chunk accumulators, or every chunk has one slot and is summed whole).
+  const ChunkParts* parts = nullptr;
+  uint64_t part0 = 0;  // the walk's first place in the partial sums (behind a tile walk's)
 };
 
 // A slot table as runs, built on the host (plan.cpp) and expanded on the
@@ -172,10 +189,12 @@ struct LaunchCfg {
   int order_verify = 0, order_checksum = 0;
 };
 
-// Device scratch owned by a plan: per-chunk accumulators (G per chunk, see
-// accumulators_per_chunk), a second set for the replica compare's sums of
-// arena B, and one 32-bit flag per chunk.  Every operation clears what it
-// uses first, so operations on one plan must not overlap in time.
+// Device scratch owned by a plan: partial sums, one place per slot of the
+// longest walk (the delta calls use the same memory as G accumulators per
+// chunk, see accumulators_per_chunk), a second set for the replica compare's
+// sums of arena B and unpack's parameter images, and one 32-bit flag per
+// chunk.  Every operation writes or clears what it reads, so what an earlier
+// one left does not matter; operations on one plan must not overlap in time.
 struct Scratch {
   fr_chunk_sum* acc = nullptr;
   fr_chunk_sum* acc_b = nullptr;
@@ -284,6 +303,12 @@ inline uint32_t slice_bytes(uint64_t C, int tile) {
   return C < t ? uint32_t(C) : t;
 }
 uint64_t accumulators_per_chunk(uint64_t C, int tile);
+// log2 of the slices of a whole chunk of C bytes.
+inline uint32_t slices_shift(uint64_t C, int tile) {
+  uint32_t sh = 0;
+  while ((uint64_t(slice_bytes(C, tile)) << sh) < C) sh++;
+  return sh;
+}
 
 // The line-aligned mode an operation with this tile and line setting walks
 // in: the setting when some chunk starts inside a line of the side it keys
@@ -300,7 +325,8 @@ struct PackBlocks {
   const SrcUnit* units = nullptr;   // sent chunks in payload order (c = global chunk id)
   const uint32_t* first = nullptr;  // per block, XCD-major: the unit holding its first vector
   uint64_t n_units = 0, n_blocks = 0, stride = 0, pay_vecs = 0;
-  SlotTable extra{};  // the chunks without payload, ids into the plan's d_units
+  SlotTable extra{};  // the chunks without payload, ids into the plan's d_units; its `parts`
+                      // cover the tiles' chunks too
 };
 // Pack walked by blocks of the payload, unpack by blocks of the receiver
 // arena (tiles of the side written).
@@ -318,7 +344,8 @@ struct UnpackBlocks {
   const PlainUnit* units = nullptr;
   const uint64_t* blocks = nullptr;  // XCD-major: (tile index << 32) | first unit in it
   uint64_t n_units = 0, n_blocks = 0, stride = 0;
-  SlotTable derived{};  // derived groups only, ids into the plan's d_derived
+  SlotTable derived{};  // derived groups only, ids into the plan's d_derived; its `parts`
+                        // cover the tiles' chunks too
 };
 
 // Kernel launchers (kernels.hip).  They assume validated arguments, enqueue
@@ -367,6 +394,19 @@ int static_scratch_address(int device, void** out);
 // (device arrays; first[0] = 0, first[n_runs] = n, no empty run).
 int launch_expand_slots(const uint64_t* first, const uint64_t* base, uint64_t n_runs, uint64_t n,
                         uint64_t stride, uint64_t* out, void* stream);
+// out[chunk] <- its slots, from the same runs: a unit is the chunk of its own
+// index (derived and plain NULL), or an unpack unit, whose derived groups of
+// 2^spc_shift slots per master chunk cover three chunks.  (Weak, like the
+// other launchers marked so: host-only builds of the plan code, which have
+// no kernels and create no plan, link without them.)
+#define FR_WEAK __attribute__((weak))
+FR_WEAK int launch_slot_parts(const uint64_t* first, const uint64_t* base, uint64_t n_runs,
+                      const DerivedUnit* derived, const PlainUnit* plain, uint32_t spc_shift,
+                      ChunkParts* out, void* stream);
+// out[chunk] <- its places in a walk of payload tiles (pack) or of receiver
+// tiles (unpack; each unit's dlead holds the rank of its first tile).
+FR_WEAK int launch_pack_tile_parts(const PackBlocks& pb, uint32_t tile_vecs, ChunkParts* out, void* stream);
+FR_WEAK int launch_unpack_tile_parts(const UnpackBlocks& ub, uint32_t tile_vecs, ChunkParts* out, void* stream);
 
 }  // namespace fr
 
@@ -382,6 +422,7 @@ struct fr_plan {
     uint32_t sl = 0;
     fr::SlotTable t{};  // t.shift: the line-aligned mode (0 off, 1 arena lines, 2 payload lines)
     uint64_t* mem = nullptr;
+    fr::ChunkParts* parts = nullptr;
     bool arena_order = false;  // units in arena address order rather than chunk (payload) order
   };
   bool chunks_in_arena_order = true;  // chunk order is already arena address order
@@ -405,6 +446,7 @@ struct fr_plan {
   fr::PlainUnit* d_plain = nullptr;      // unpack units: plain chunks
   uint32_t n_plain = 0;
   void* d_scratch = nullptr;         // one allocation holding `scratch`
+  uint64_t n_places = 0;             // partial sums the longest walk stores
   // Delta lists, built on the device (one allocation, carved at creation):
   void* d_delta = nullptr;
   fr::ChunkLoc* d_delta_loc = nullptr;  // per chunk id

@@ -70,6 +70,14 @@ constexpr uint32_t kDefaultAbsorbPack = 1, kDefaultAbsorbUnpack = 1, kDefaultAbs
 // host knows only its largest possible length): 256 per CU.
 constexpr uint32_t kDefaultDeltaGrid = 65536;
 
+// Walks with one slot per chunk store the chunks' sums themselves, with no
+// partial sums to fold, in states of at most this many chunks.  Sums of
+// neighbouring chunks then share cache lines that several XCDs write, which
+// costs more than the fold in larger ones (the checksum of 478,319 chunks of
+// 16 KiB: 1,180 us against 1,099 and 6 for the fold); below, the fold's
+// launch (4 us, and as much on the host) is the larger part.
+constexpr uint64_t kWholeChunks = 32768;
+
 static uint64_t esize(uint32_t dtype) { return dtype == FR_F32 ? 4 : 2; }
 static uint64_t align16(uint64_t x) { return (x + 15) & ~uint64_t(15); }
 static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) & ~(a - 1); }
@@ -218,11 +226,13 @@ static int hip_fail(hipError_t e) {
 // the null stream, and frees nothing on success (hipFree waits for the whole
 // device), so that creating a plan does not stall other work on the device.
 // `runs` stages the run descriptions of the slot tables; it points into the
-// plan's scratch, which no call has used yet and every call clears first.
+// memory of the delta calls' unit records, which no call has used yet and
+// every delta call writes before reading.
 struct Staging {
   hipStream_t s = nullptr;
   uint64_t* runs = nullptr;
   uint64_t runs_cap = 0;  // in uint64_t
+  ChunkParts* parts = nullptr;  // the next walk's (the plan's memory)
   ~Staging() {
     if (s) (void)hipStreamDestroy(s);
   }
@@ -265,7 +275,10 @@ namespace {
 
 // Allocates the slot table of `r` on the device and expands it there: the
 // host uploads one (first slot, base) pair per run instead of every slot.
-int upload_walk(const SlotRuns& r, fr_plan::Walk& w, const Staging& st) {
+// With `parts`, also writes there where each of the runs' chunks has its
+// partial sums (launch_slot_parts; the unpack's units, or NULL).
+int upload_walk(const SlotRuns& r, fr_plan::Walk& w, const Staging& st, ChunkParts* parts = nullptr,
+                const fr_plan* unpack = nullptr) {
   w.sl = r.sl;
   w.t.n = r.n();
   w.t.stride = r.stride();
@@ -283,6 +296,11 @@ int upload_walk(const SlotRuns& r, fr_plan::Walk& w, const Staging& st) {
                        st.s);
   if (e == hipSuccess)
     e = hipError_t(launch_expand_slots(d_first, d_base, n_runs, r.n(), r.stride(), w.mem, st.s));
+  if (e == hipSuccess && parts)
+    e = hipError_t(launch_slot_parts(d_first, d_base, n_runs, unpack ? unpack->d_derived : nullptr,
+                                     unpack ? unpack->d_plain : nullptr,
+                                     unpack ? slices_shift(unpack->layout.C, unpack->cfg.tile_unpack) : 0,
+                                     parts, st.s));
   if (e == hipSuccess) e = hipStreamSynchronize(st.s);
   return e == hipSuccess ? FR_OK : hip_fail(e);
 }
@@ -297,12 +315,14 @@ extern "C" int fr_plan_destroy(fr_plan* p) {
     switched = hipSetDevice(p->device) == hipSuccess;
   }
   if (p->d_units) (void)hipFree(p->d_units);
-  for (auto& w : p->src_walks)
+  auto free_walk = [](fr_plan::Walk& w) {
     if (w.mem) (void)hipFree(w.mem);
-  if (p->unpack_walk.mem) (void)hipFree(p->unpack_walk.mem);
-  if (p->pack_extra.mem) (void)hipFree(p->pack_extra.mem);
+  };
+  for (auto& w : p->src_walks) free_walk(w);
+  free_walk(p->unpack_walk);
+  free_walk(p->pack_extra);
   if (p->d_blocks) (void)hipFree(p->d_blocks);
-  if (p->unpack_derived.mem) (void)hipFree(p->unpack_derived.mem);
+  free_walk(p->unpack_derived);
   if (p->d_ublocks) (void)hipFree(p->d_ublocks);
   if (p->d_derived) (void)hipFree(p->d_derived);
   if (p->d_plain) (void)hipFree(p->d_plain);
@@ -472,6 +492,19 @@ void unpack_units(const fr_tensor_desc* table, uint32_t n, const Layout& L,
   }
 }
 
+// Room for where each chunk's partial sums lie in a walk (build_delta's
+// allocation holds it for every walk).
+void take_parts(fr_plan::Walk& w, const Layout& L, Staging& st) {
+  w.t.parts = w.parts = st.parts;
+  st.parts += L.n_chunks;
+}
+
+// The plan's partial sums must hold a walk's places: `tiles` of a tile walk,
+// then one per entry of the slot table.
+void need_places(fr_plan* p, const SlotTable& t, uint64_t tiles) {
+  p->n_places = std::max(p->n_places, tiles + 8 * t.stride);
+}
+
 // Walks of pack / checksum / compare: every chunk once, one table per slice
 // size, alignment, lead handling and order their configurations use (a
 // line-aligned walk is the plain one when every chunk starts on a line).
@@ -479,7 +512,7 @@ void unpack_units(const fr_tensor_desc* table, uint32_t n, const Layout& L,
 // only reads the arenas, walks them in address order by default (the same
 // unless the table lists its tensors out of arena order; the checksum
 // measured slower that way, see kDefaultOrderVerify).
-int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, const Staging& st) {
+int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st) {
   const Layout& L = p->layout;
   struct Want {
     int tile, line, absorb;
@@ -521,11 +554,16 @@ int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, const Staging
       b.add(c, units[c].len + (absorb ? 0 : lead_bytes(units[c].lead, units[c].plead, shift, sl)), 0);
     }
     p->src_walks.emplace_back();
-    const int rc = upload_walk(b, p->src_walks.back(), st);
-    p->src_walks.back().t.shift = shift;
-    p->src_walks.back().t.absorb = absorb;
-    p->src_walks.back().arena_order = arena;
+    fr_plan::Walk& w = p->src_walks.back();
+    w.t.shift = shift;
+    w.t.absorb = absorb;
+    w.arena_order = arena;
+    // with one slot per chunk a slice's sums are the chunk's: a small state
+    // needs no partial sums
+    if (b.n() != L.n_chunks || L.n_chunks > kWholeChunks) take_parts(w, L, st);
+    const int rc = upload_walk(b, w, st, w.parts);
     if (rc != FR_OK) return rc;
+    need_places(p, w.t, 0);
   }
   return FR_OK;
 }
@@ -533,7 +571,7 @@ int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, const Staging
 // Pack by blocks of the payload (PackBlocks): the sent chunks' units in
 // payload order, each block's first unit (found on the device), and a plain
 // walk of the chunks without payload.
-int build_pack_blocks(fr_plan* p, const std::vector<SrcUnit>& units, const Staging& st) {
+int build_pack_blocks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st) {
   const Layout& L = p->layout;
   const uint32_t block_vecs = tile_bytes(p->cfg.tile_pack) / 16;
   std::vector<SrcUnit> pay;
@@ -564,7 +602,15 @@ int build_pack_blocks(fr_plan* p, const std::vector<SrcUnit>& units, const Stagi
       if (e != hipSuccess) rc = hip_fail(e);
     }
   }
-  if (rc == FR_OK) rc = upload_walk(b, p->pack_extra, st);
+  take_parts(p->pack_extra, L, st);
+  if (rc == FR_OK) rc = upload_walk(b, p->pack_extra, st, p->pack_extra.parts);
+  if (rc == FR_OK) {
+    hipError_t e = hipError_t(launch_pack_tile_parts(pb, block_vecs, p->pack_extra.parts, st.s));
+    if (e == hipSuccess) e = hipStreamSynchronize(st.s);
+    if (e != hipSuccess) rc = hip_fail(e);
+  }
+  p->pack_extra.t.part0 = 16 * pb.stride + pb.n_units;  // behind the tiles' (tile_place)
+  need_places(p, p->pack_extra.t, p->pack_extra.t.part0);
   pb.extra = p->pack_extra.t;
   return rc;
 }
@@ -574,7 +620,7 @@ int build_pack_blocks(fr_plan* p, const std::vector<SrcUnit>& units, const Stagi
 // the first chunk touching each (XCD-major), and the walk of the derived
 // groups in table order (ids into d_derived, as unpack_units lists them).
 int build_unpack_blocks(fr_plan* p, const std::vector<ChunkRec>& recs,
-                        const std::vector<uint8_t>& is_master, const Staging& st) {
+                        const std::vector<uint8_t>& is_master, Staging& st) {
   const Layout& L = p->layout;
   const uint64_t tile_vecs = tile_bytes(p->cfg.tile_unpack) / 16;
   SlotRuns b;
@@ -606,14 +652,17 @@ int build_unpack_blocks(fr_plan* p, const std::vector<ChunkRec>& recs,
   }
   // (tile << 32) | first unit touching it, for every tile some unit touches,
   // in receiver order, stored XCD-major: counted, then written
+  // (dlead: the rank of the unit's first tile among those listed)
   auto each_tile = [&](auto&& emit) {
-    uint64_t last = ~uint64_t(0);
+    uint64_t last = ~uint64_t(0), rank = 0;  // tiles listed so far
     for (uint64_t u = 0; u < units.size(); u++) {
       const uint64_t v0 = units[u].dst_off / 16, v1 = v0 + (units[u].len + 15) / 16;
+      units[u].dlead = uint32_t(rank && last == v0 / tile_vecs ? rank - 1 : rank);
       for (uint64_t t = v0 / tile_vecs; t * tile_vecs < v1; t++)
         if (last == ~uint64_t(0) || last < t) {
           emit((t << 32) | u);
           last = t;
+          rank++;
         }
     }
   };
@@ -638,7 +687,16 @@ int build_unpack_blocks(fr_plan* p, const std::vector<ChunkRec>& recs,
     rc = copy_in(q, units.data(), units.size() * sizeof(PlainUnit), st.s);
     if (rc == FR_OK) rc = copy_in(q + b_units, xcd.data(), xcd.size() * sizeof(uint64_t), st.s);
   }
-  if (rc == FR_OK) rc = upload_walk(b, p->unpack_derived, st);
+  take_parts(p->unpack_derived, L, st);
+  if (rc == FR_OK) rc = upload_walk(b, p->unpack_derived, st, p->unpack_derived.parts, p);
+  if (rc == FR_OK) {
+    hipError_t e =
+        hipError_t(launch_unpack_tile_parts(ub, uint32_t(tile_vecs), p->unpack_derived.parts, st.s));
+    if (e == hipSuccess) e = hipStreamSynchronize(st.s);
+    if (e != hipSuccess) rc = hip_fail(e);
+  }
+  p->unpack_derived.t.part0 = 16 * ub.stride + ub.n_units;
+  need_places(p, p->unpack_derived.t, p->unpack_derived.t.part0);
   ub.derived = p->unpack_derived.t;
   return rc;
 }
@@ -646,7 +704,7 @@ int build_unpack_blocks(fr_plan* p, const std::vector<ChunkRec>& recs,
 // Walk of unpack, in payload (table) order: a derived entry's groups (their
 // master bytes) where the entry stands, plain chunks where theirs.
 int build_unpack_walk(fr_plan* p, const std::vector<ChunkRec>& recs,
-                      const std::vector<uint8_t>& is_master, const Staging& st) {
+                      const std::vector<uint8_t>& is_master, Staging& st) {
   const Layout& L = p->layout;
   SlotRuns b;
   b.sl = slice_bytes(L.C, p->cfg.tile_unpack);
@@ -671,31 +729,32 @@ int build_unpack_walk(fr_plan* p, const std::vector<ChunkRec>& recs,
       }
     }
   }
-  const int rc = upload_walk(b, p->unpack_walk, st);
+  take_parts(p->unpack_walk, L, st);
+  const int rc = upload_walk(b, p->unpack_walk, st, p->unpack_walk.parts, p);
   p->unpack_walk.t.shift = line;
   p->unpack_walk.t.absorb = absorb;
+  need_places(p, p->unpack_walk.t, 0);
   return rc;
 }
 
-// Scratch: accumulators for the largest G any configured tile needs, for two
-// arenas, and one flag per chunk.  Its accumulators (16 bytes per chunk at
-// least, twice) also hold the staged runs of each slot table (at most one
-// run per chunk: 16 bytes per run, and 8 more).
-int build_scratch(fr_plan* p, Staging* st) {
+// Scratch: two sets of partial sums, one place per slot of the longest walk
+// (16 bytes per 4 KiB slice: 0.4 % of the state each), which also hold the
+// delta calls' accumulators (the largest G their tiles need per chunk), and
+// one flag per chunk.
+int build_scratch(fr_plan* p, const Staging& st) {
   const Layout& L = p->layout;
   uint64_t g = 1;
-  for (int t : {p->cfg.tile_pack, p->cfg.tile_unpack, p->cfg.tile_verify, p->cfg.tile_checksum})
+  for (int t : {p->cfg.tile_pack, p->cfg.tile_unpack})
     g = std::max<uint64_t>(g, accumulators_per_chunk(L.C, t));
-  const uint64_t acc_bytes = L.n_chunks * g * sizeof(fr_chunk_sum);
+  const uint64_t acc_bytes =
+      (std::max(L.n_chunks * g, p->n_places) * sizeof(fr_chunk_sum) + 255) & ~uint64_t(255);
   const uint64_t flag_bytes = (L.n_chunks * 4 + 255) & ~uint64_t(255);
-  const int rc = upload(nullptr, 2 * acc_bytes + flag_bytes, &p->d_scratch, st->s);
+  const int rc = upload(nullptr, 2 * acc_bytes + flag_bytes, &p->d_scratch, st.s);
   if (rc == FR_OK && p->d_scratch) {
     uint8_t* base = static_cast<uint8_t*>(p->d_scratch);
     p->scratch.acc = reinterpret_cast<fr_chunk_sum*>(base);
     p->scratch.acc_b = reinterpret_cast<fr_chunk_sum*>(base + acc_bytes);
     p->scratch.flags = reinterpret_cast<uint32_t*>(base + 2 * acc_bytes);
-    st->runs = reinterpret_cast<uint64_t*>(base);
-    st->runs_cap = 2 * acc_bytes / sizeof(uint64_t);
   }
   return rc;
 }
@@ -705,8 +764,10 @@ int build_scratch(fr_plan* p, Staging* st) {
 // (pack's one per chunk, or unpack's plain and derived ones), the scan state,
 // and the staging of a list given on the host (pinned, so that its upload
 // is asynchronous; an event marks when the staging may be refilled).
-// Allocated once here, so that no delta call allocates.
-int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, const Staging& st) {
+// Allocated once here, so that no delta call allocates.  The records' memory
+// stages the slot tables' runs while the plan is built, and the same
+// allocation holds where each chunk's partial sums lie in each walk.
+int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
   const Layout& L = p->layout;
   const uint64_t nc = L.n_chunks, nb = (nc + kListBlock - 1) / kListBlock, nw = (nc + 31) / 32;
   auto up = [](uint64_t b) { return (b + 255) & ~uint64_t(255); };
@@ -715,7 +776,9 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, const Staging& st
                                                               (nc - L.n_sent_chunks) * sizeof(DerivedUnit)));
   const uint64_t b_agg = up(nb * sizeof(DeltaAgg)), b_pre = up(nb * sizeof(DeltaPre));
   const uint64_t b_counts = 256, b_bits = up(nw * 4), b_ids = up(nc * 4), b_payof = up(nc * 8);
-  const uint64_t total = b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids;
+  const uint64_t b_parts = up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
+  const uint64_t total =
+      b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids + b_parts;
   int rc = upload(nullptr, total, &p->d_delta, st.s);
   if (rc != FR_OK) return rc;
   uint8_t* q = static_cast<uint8_t*>(p->d_delta);
@@ -726,6 +789,8 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, const Staging& st
   };
   p->d_delta_loc = reinterpret_cast<ChunkLoc*>(take(b_loc));
   uint8_t* units = take(b_units);
+  st.runs = reinterpret_cast<uint64_t*>(units);  // at most one run per chunk: 16 bytes each, and 8 more
+  st.runs_cap = b_units / sizeof(uint64_t);
   p->d_delta_src = reinterpret_cast<SrcUnit*>(units);
   p->d_delta_plain = reinterpret_cast<PlainUnit*>(units);
   p->d_delta_derived = reinterpret_cast<DerivedUnit*>(units + L.n_sent_chunks * sizeof(PlainUnit));
@@ -736,6 +801,7 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, const Staging& st
   p->d_delta_ids = reinterpret_cast<uint32_t*>(take(b_ids));
   p->d_delta_payof = reinterpret_cast<uint64_t*>(take(b_payof));
   p->d_delta_m0 = reinterpret_cast<uint32_t*>(take(b_ids));
+  st.parts = reinterpret_cast<ChunkParts*>(take(b_parts));
   std::vector<ChunkLoc> loc(nc);
   std::vector<uint32_t> m0(nc, 0);
   for (uint32_t k = 0; k < p->table.size(); k++) {
@@ -819,19 +885,19 @@ extern "C" int fr_plan_create_ex(const fr_tensor_desc* table, uint32_t n, uint64
       delete p;
       return hip_fail(es);
     }
-    rc = build_scratch(p, &st);
+    rc = build_delta(p, recs, st);
     if (rc == FR_OK)
       rc = upload(units.data(), units.size() * sizeof(SrcUnit), (void**)&p->d_units, st.s);
-    if (rc == FR_OK) rc = build_src_walks(p, units, st);
-    if (rc == FR_OK && p->cfg.line_pack == kLineBlocks) rc = build_pack_blocks(p, units, st);
-    if (rc == FR_OK && p->cfg.line_unpack != kLineBlocks) rc = build_unpack_walk(p, recs, is_master, st);
-    if (rc == FR_OK && p->cfg.line_unpack == kLineBlocks) rc = build_unpack_blocks(p, recs, is_master, st);
     if (rc == FR_OK)
       rc = upload(derived.data(), derived.size() * sizeof(DerivedUnit), (void**)&p->d_derived,
                   st.s);
     if (rc == FR_OK)
       rc = upload(plain.data(), plain.size() * sizeof(PlainUnit), (void**)&p->d_plain, st.s);
-    if (rc == FR_OK) rc = build_delta(p, recs, st);
+    if (rc == FR_OK) rc = build_src_walks(p, units, st);
+    if (rc == FR_OK && p->cfg.line_pack == kLineBlocks) rc = build_pack_blocks(p, units, st);
+    if (rc == FR_OK && p->cfg.line_unpack != kLineBlocks) rc = build_unpack_walk(p, recs, is_master, st);
+    if (rc == FR_OK && p->cfg.line_unpack == kLineBlocks) rc = build_unpack_blocks(p, recs, is_master, st);
+    if (rc == FR_OK) rc = build_scratch(p, st);
     if (rc != FR_OK) {
       fr_plan_destroy(p);
       return rc;

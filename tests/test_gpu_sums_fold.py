@@ -1,0 +1,42 @@
+"""Chunk sums folded from the partial sums that the main kernels store: every
+number of slices a chunk can have in the folds' ranges (one, up to 8, 16 and
+more slices per whole chunk), one slice more or less, tiles that begin with
+other chunks, and small and large chunk counts, against the CPU oracle (all
+outputs bit for bit, with a corrupted wire)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2509_03047_amd import workloads as W  # noqa: E402
+from tests.test_gpu_parity_small import _check_against_oracle  # noqa: E402
+
+
+def _table(C, rng, align):
+    """Derived pairs and plain entries whose sizes lie around whole chunks and
+    whole 4 KiB and 16 KiB slices, at offsets that are multiples of `align`."""
+    sizes = sorted({b + d for b in (16, 4096, 16384, C, C + 4096, 2 * C, 2 * C + 16384, 3 * C - 4096)
+                    for d in (-4, 0, 4) if b + d > 0})
+    rows, so, do = [], 0, 0
+    up = lambda x: -(-x // align) * align  # noqa: E731
+    for k, nb in enumerate(sizes):
+        n = nb // 4
+        if k % 3 == 0:  # a bf16 image of 2 n bytes and its master of 4 n
+            i = len(rows)
+            rows.append([so, do, n, W.BF16, i + 1])
+            so, do = up(so + 2 * n), up(do + 2 * n + 32)
+        rows.append([so, do, n, W.F32, -1])
+        so, do = up(so + 4 * n + 16 * (k % 2)), up(do + 4 * n)
+    return np.array([tuple(r) for r in rows], dtype=W.TABLE_DTYPE), so, do
+
+
+@pytest.mark.parametrize("align", [16, 128])
+@pytest.mark.parametrize("C", [16, 1 << 12, 1 << 13, 1 << 14, 1 << 15, 1 << 16, 1 << 17, 1 << 18, 1 << 20])
+def test_partial_sums_fold_to_the_oracle(C, align):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(C + align)
+    t, sb, db = _table(C, rng, align)
+    src = W.random_tiny_state(t, sb, rng)
+    _check_against_oracle(t, C, src, sb, db, corrupt_rng=rng, tag=f"fold C={C} align={align}")
