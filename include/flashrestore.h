@@ -151,7 +151,8 @@ typedef struct fr_plan_info {
                                aligned tile of the side written (the payload for
                                pack, the receiver arena for unpack) per workgroup,
                                the default where that side's chunks start inside
-                               cache lines; FR_WALK_* */
+                               cache lines; FR_WALK_*.  (Of states too large to
+                               take whole chunks, see fr_plan_create) */
   uint32_t tile_pack;       /* the tile each operation launches with, 0-10 (threads x */
   uint32_t tile_unpack;     /* 16-byte vectors per workgroup: 256x1, 512x1, 256x2, */
   uint32_t tile_verify;     /* 256x4, 64x4, 128x2, 64x2, 64x1, 128x1, 128x4, 64x8): */
@@ -204,12 +205,16 @@ typedef struct fr_plan_info {
  * reports the walks pack and unpack take and every operation's tile).  FLASHRESTORE_ABSORB_PACK / _UNPACK
  * / _VERIFY / _CHECKSUM (defaults 1, 1, 0, 0): a cut slice walk gives a
  * chunk's last slice its leftover lead instead of one more slice.
- * FLASHRESTORE_BUF_PACK / _UNPACK / _VERIFY / _CHECKSUM (default 0): slice
- * walks load through buffer resources, all of a thread's loads in flight
+ * FLASHRESTORE_BUF_PACK / _UNPACK / _VERIFY / _CHECKSUM (default 0; the
+ * compare with sums 1): slice walks load through buffer resources, all of a thread's loads in flight
  * at once.  FLASHRESTORE_ORDER_VERIFY / _CHECKSUM (defaults 1, 0): the
  * compare's or the checksum's slices in arena address order rather than
  * chunk order (they differ for tables that list tensors out of arena
- * order).  FLASHRESTORE_MAX_GRID caps the workgroups per launch (0 or
+ * order).  Where none of these is set, small states (and some chunk sizes)
+ * take one whole chunk per workgroup in an operation instead of its walk and
+ * tile; FLASHRESTORE_SMALL gives the largest state, in bytes, that does so in
+ * every operation (0: none; chunks up to 64 KiB only) in place of the built-in
+ * rule.  FLASHRESTORE_MAX_GRID caps the workgroups per launch (0 or
  * unset: one per slice or tile). */
 int fr_plan_create(const fr_tensor_desc* table, uint32_t n_entries, uint64_t chunk_bytes,
                    uint64_t src_arena_bytes, uint64_t dst_arena_bytes, fr_plan** out);

@@ -109,6 +109,18 @@ const SlotTable* src_walk(const fr_plan* plan, int tile, int line, int absorb, b
   return nullptr;
 }
 
+// An operation over the plan's whole chunks, to be completed.
+SmallArgs small_args(const fr_plan* plan, SmallArgs::Op op) {
+  SmallArgs m;
+  m.op = op;
+  m.cfg = plan->cfg;
+  m.C = plan->layout.C;
+  m.n_chunks = uint32_t(plan->layout.n_chunks);
+  m.units = plan->d_units;
+  m.flags = plan->scratch.flags;
+  return m;
+}
+
 #define FR_TRY(expr)            \
   do {                          \
     const int rc_ = (expr);     \
@@ -129,6 +141,13 @@ extern "C" int fr_pack_state(const fr_plan* plan, const void* src_base, void* pa
   const Region outs[] = {{payload, L.payload_bytes}, {sums, L.n_chunks * sizeof(fr_chunk_sum)}};
   const Region ins[] = {{src_base, plan->src_arena_bytes}};
   FR_TRY(check_disjoint(outs, 2, ins, 1));
+  if (plan->cfg.small & kSmallPack) {
+    SmallArgs m = small_args(plan, SmallArgs::kPack);
+    m.src = src_base;
+    m.payload = payload;
+    m.sums = sums;
+    return launch_result(launch_small(m, stream));
+  }
   if (plan->cfg.line_pack == kLineBlocks)
     return launch_result(launch_pack_blocks(plan->d_units, plan->pack_blocks, uint32_t(L.n_chunks),
                                             L.C, src_base, payload, sums, plan->scratch, plan->cfg,
@@ -155,6 +174,19 @@ extern "C" int fr_unpack_state(const fr_plan* plan, const void* payload, const f
   const Region outs[] = {{dst_base, plan->dst_arena_bytes}, {bad_bitmap, words * 4}, {n_bad, 8}};
   const Region ins[] = {{payload, L.payload_bytes}, {sums, L.n_chunks * sizeof(fr_chunk_sum)}};
   FR_TRY(check_disjoint(outs, 3, ins, 2));
+  if (plan->cfg.small & kSmallUnpack) {
+    SmallArgs m = small_args(plan, SmallArgs::kUnpack);
+    m.derived = plan->d_derived;
+    m.n_derived = plan->n_derived;
+    m.plain = plan->d_plain;
+    m.n_plain = plan->n_plain;
+    m.src = payload;
+    m.dst = dst_base;
+    m.sent = sums;
+    m.bitmap = bad_bitmap;
+    m.count = n_bad;
+    return launch_result(launch_small(m, stream));
+  }
   UnpackArgs u;
   u.derived = plan->d_derived;
   u.n_derived = plan->n_derived;
@@ -176,8 +208,13 @@ extern "C" int fr_unpack_state(const fr_plan* plan, const void* payload, const f
 
 namespace {
 
+// Whether the compare takes one whole chunk per workgroup.
+bool verify_whole(const fr_plan* plan, const fr_chunk_sum* sums_a) {
+  return plan->cfg.small & (sums_a ? kSmallVerifySums : kSmallVerify);
+}
+
 // Argument checks of the replica compare (both entry points); on success
-// *walk is the plan's compare walk.
+// *walk is the plan's compare walk (none where it takes whole chunks).
 int verify_checks(const fr_plan* plan, const void* base_a, const void* base_b,
                   uint32_t* diff_bitmap, uint64_t* n_diff, fr_chunk_sum* sums_a,
                   fr_chunk_sum* sums_b, hipStream_t stream, const SlotTable** walk) {
@@ -198,9 +235,25 @@ int verify_checks(const fr_plan* plan, const void* base_a, const void* base_b,
   const Region outs[] = {{diff_bitmap, words * 4}, {n_diff, 8}, {sums_a, sb}, {sums_b, sb}};
   const Region ins[] = {{base_a, plan->src_arena_bytes}, {base_b, plan->src_arena_bytes}};
   FR_TRY(check_disjoint(outs, 4, ins, 2));
+  if (verify_whole(plan, sums_a)) return FR_OK;
   *walk = src_walk(plan, plan->cfg.tile_verify, plan->cfg.line_verify, plan->cfg.absorb_verify,
                    plan->cfg.order_verify != 0);
   return *walk ? FR_OK : FR_E_INVAL;
+}
+
+// The compare by whole chunks, its flags in `flags` (4 bytes per chunk).
+int verify_small(const fr_plan* plan, const void* a, const void* b, uint32_t* bitmap,
+                 uint64_t* n_diff, fr_chunk_sum* sums_a, fr_chunk_sum* sums_b, uint32_t* flags,
+                 hipStream_t stream) {
+  SmallArgs m = small_args(plan, SmallArgs::kVerify);
+  m.src = a;
+  m.src_b = b;
+  m.sums = sums_a;
+  m.sums_b = sums_b;
+  m.flags = flags;
+  m.bitmap = bitmap;
+  m.count = n_diff;
+  return launch_result(launch_small(m, stream));
 }
 
 }  // namespace
@@ -211,6 +264,9 @@ extern "C" int fr_verify_replicas(const fr_plan* plan, const void* base_a, const
   const SlotTable* walk = nullptr;
   FR_TRY(verify_checks(plan, base_a, base_b, diff_bitmap, n_diff, sums_a, sums_b, stream, &walk));
   const Layout& L = plan->layout;
+  if (verify_whole(plan, sums_a))
+    return verify_small(plan, base_a, base_b, diff_bitmap, n_diff, sums_a, sums_b,
+                        plan->scratch.flags, stream);
   return launch_result(launch_verify(plan->d_units, *walk, uint32_t(L.n_chunks), L.C, base_a,
                                      base_b, diff_bitmap, n_diff, sums_a, sums_b, plan->scratch,
                                      plan->cfg, stream));
@@ -253,6 +309,9 @@ extern "C" int fr_verify_replicas_noalloc(const fr_plan* plan, const void* base_
   const int e = static_scratch_address(plan->device, &base);  // the plan's device is current
   if (e != 0) return device_error(hipError_t(e));
   uint8_t* p = static_cast<uint8_t*>(base);
+  if (verify_whole(plan, sums_a))
+    return verify_small(plan, base_a, base_b, diff_bitmap, n_diff, sums_a, sums_b,
+                        reinterpret_cast<uint32_t*>(p), stream);
   Scratch scr;
   scr.flags = reinterpret_cast<uint32_t*>(p);
   scr.acc = reinterpret_cast<fr_chunk_sum*>(p + flag_bytes);
@@ -274,6 +333,12 @@ extern "C" int fr_checksum_state(const fr_plan* plan, const void* base, fr_chunk
   const Region outs[] = {{sums, L.n_chunks * sizeof(fr_chunk_sum)}};
   const Region ins[] = {{base, plan->src_arena_bytes}};
   FR_TRY(check_disjoint(outs, 1, ins, 1));
+  if (plan->cfg.small & kSmallChecksum) {
+    SmallArgs m = small_args(plan, SmallArgs::kChecksum);
+    m.src = base;
+    m.sums = sums;
+    return launch_result(launch_small(m, stream));
+  }
   const SlotTable* walk =
       src_walk(plan, plan->cfg.tile_checksum, plan->cfg.line_checksum, plan->cfg.absorb_checksum,
                plan->cfg.order_checksum != 0);

@@ -183,11 +183,16 @@ struct LaunchCfg {
   int absorb_pack = 0, absorb_unpack = 0, absorb_verify = 0, absorb_checksum = 0;
   // slices loaded through buffer resources (every load of a thread in
   // flight at once) rather than predicated global loads
-  int buf_pack = 0, buf_unpack = 0, buf_verify = 0, buf_checksum = 0;
+  // (buf_sums: the compare's with sums)
+  int buf_pack = 0, buf_unpack = 0, buf_verify = 0, buf_sums = 1, buf_checksum = 0;
   // the compare's and the checksum's walks in arena address order rather
   // than chunk order (they differ when a table lists tensors out of arena order)
   int order_verify = 0, order_checksum = 0;
+  // operations that take one whole chunk per workgroup (kSmall*)
+  uint32_t small = 0;
 };
+constexpr uint32_t kSmallPack = 1, kSmallUnpack = 2, kSmallVerify = 4, kSmallVerifySums = 8,
+                   kSmallChecksum = 16, kSmallAll = 31;
 
 // Device scratch owned by a plan: partial sums, one place per slot of the
 // longest walk (the delta calls use the same memory as G accumulators per
@@ -348,8 +353,36 @@ struct UnpackBlocks {
                         // cover the tiles' chunks too
 };
 
+// An operation of a small state, one whole chunk per workgroup: the largest
+// chunk a workgroup of 1024 threads holds (four 16-byte vectors a thread).
+constexpr uint64_t kSmallChunk = uint64_t(1) << 16;
+struct SmallArgs {
+  enum Op { kPack, kChecksum, kVerify, kUnpack } op = kPack;
+  LaunchCfg cfg;
+  uint64_t C = 0;
+  uint32_t n_chunks = 0;
+  const SrcUnit* units = nullptr;  // pack, checksum, compare: chunk order
+  const DerivedUnit* derived = nullptr;
+  const PlainUnit* plain = nullptr;
+  uint32_t n_derived = 0, n_plain = 0;
+  const void* src = nullptr;    // arena read; unpack: the payload
+  const void* src_b = nullptr;  // compare: the second arena
+  void* payload = nullptr;
+  void* dst = nullptr;
+  const fr_chunk_sum* sent = nullptr;
+  fr_chunk_sum* sums = nullptr;  // compare: NULL or the first arena's
+  fr_chunk_sum* sums_b = nullptr;
+  uint32_t* flags = nullptr;  // one per chunk (scratch)
+  uint32_t* bitmap = nullptr;
+  uint64_t* count = nullptr;
+};
+
 // Kernel launchers (kernels.hip).  They assume validated arguments, enqueue
-// on `stream` and return the hipError_t of the launches as an int.
+// on `stream` and return the hipError_t of the launches as an int.  (Those
+// marked weak: host-only builds of the plan code and the entry points, which
+// have no kernels and create no plan, link without them.)
+#define FR_WEAK __attribute__((weak))
+FR_WEAK int launch_small(const SmallArgs& args, void* stream);
 // `units` holds n_chunks records whose sums slots c cover [0, n_chunks);
 // `slots` walks them at the slice size of the operation's tile.
 int launch_pack(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunks, uint64_t C,
@@ -396,10 +429,7 @@ int launch_expand_slots(const uint64_t* first, const uint64_t* base, uint64_t n_
                         uint64_t stride, uint64_t* out, void* stream);
 // out[chunk] <- its slots, from the same runs: a unit is the chunk of its own
 // index (derived and plain NULL), or an unpack unit, whose derived groups of
-// 2^spc_shift slots per master chunk cover three chunks.  (Weak, like the
-// other launchers marked so: host-only builds of the plan code, which have
-// no kernels and create no plan, link without them.)
-#define FR_WEAK __attribute__((weak))
+// 2^spc_shift slots per master chunk cover three chunks.
 FR_WEAK int launch_slot_parts(const uint64_t* first, const uint64_t* base, uint64_t n_runs,
                       const DerivedUnit* derived, const PlainUnit* plain, uint32_t spc_shift,
                       ChunkParts* out, void* stream);

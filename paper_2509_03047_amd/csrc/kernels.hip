@@ -219,6 +219,17 @@ __device__ __forceinline__ void block_sum(u64 (&v)[K], u64 (&lds)[2][B / 64][K],
     for (int k = 0; k < K; k++) lds[parity][wave][k] = v[k];
   }
   __syncthreads();
+  if (B >= 512 || K > 4) {  // many totals: one row of lanes reads one wave's each
+    if (threadIdx.x < 16) {
+#pragma unroll
+      for (int k = 0; k < K; k++) {
+        u64 t = threadIdx.x < B / 64 ? lds[parity][threadIdx.x % (B / 64)][k] : 0;
+        t = add_dpp<0x4E>(add_dpp<0xB1>(t));
+        v[k] = add_dpp<0x128>(add_dpp<0x124>(t));
+      }
+    }
+    return;
+  }
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int k = 0; k < K; k++) {
@@ -933,6 +944,226 @@ __global__ __launch_bounds__(B) void k_verify(const SrcUnit* __restrict__ units,
       }
     }
   }
+}
+
+// ---------------------------------------------------------- small states
+//
+// A small state's operations are bound by launches (3.5 us each on the host,
+// about as much between dependent kernels) and by the chain of dependent
+// loads before the data, not by HBM.  So one workgroup takes one whole chunk
+// (unpack: one derived group or plain chunk): it reads the chunk's record,
+// then everything of the chunk at once, every load in flight together
+// through buffer resources, and ends up with the chunk's whole sums.  Pack
+// and the checksum are then one launch, and unpack and the compare leave one
+// flag per chunk to the finalize kernel.  B threads hold kSmallVecs vectors
+// each, B * 64 >= C bytes.
+constexpr int kSmallVecs = 4;
+
+__device__ __forceinline__ void st_buf2(const u32x2& v, rsrc_t r, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b64(v, r, int(off), 0, 2);
+}
+
+// The chunk's vectors q B + threadIdx.x; zeros past its whole vectors.
+template <int B>
+__device__ __forceinline__ void load_chunk(u32x4 (&x)[kSmallVecs], rsrc_t in) {
+#pragma unroll
+  for (int q = 0; q < kSmallVecs; q++) x[q] = ld_buf(in, 16 * (q * B + threadIdx.x));
+}
+
+template <int B, bool kStore>
+__global__ __launch_bounds__(B) void k_pack_chunk(const SrcUnit* __restrict__ units, u64 n,
+                                                  const uint8_t* __restrict__ src,
+                                                  uint8_t* __restrict__ payload,
+                                                  fr_chunk_sum* __restrict__ sums) {
+  __shared__ u64 lds[2][B / 64][2];
+  int parity = 0;
+  for (u64 g = blockIdx.x; g < n; g += gridDim.x) {
+    const SrcUnit r = units[g];
+    const uint32_t nvec = r.len >> 4, tail = r.len & 15;
+    const uint8_t* s = src + r.src_off;
+    u32x4 x[kSmallVecs];
+    load_chunk<B>(x, make_rsrc(s, 16 * nvec));
+    u32x4 t = u32x4{0, 0, 0, 0};
+    const bool mine = tail && threadIdx.x == nvec % B;
+    if (mine) t = load_tail(s + 16 * nvec, tail);
+    u64 acc[2] = {0, 0};
+    if (kStore && r.pay_off != kNoPayload) {
+      // the segment's zero padding is written with its tail, the gap up to
+      // the next segment (fewer vectors than the segment alignment) after it
+      const uint32_t endv = nvec + (tail ? 1u : 0u);
+      u32x4* d = reinterpret_cast<u32x4*>(payload + r.pay_off);
+      const rsrc_t out = make_rsrc(d, 16 * nvec);
+#pragma unroll
+      for (int q = 0; q < kSmallVecs; q++) st_buf(x[q], out, 16 * (q * B + threadIdx.x));
+      if (mine) d[nvec] = t;
+      for (uint32_t v = threadIdx.x; v < r.gap_v; v += B) st_nt(u32x4{0, 0, 0, 0}, d + endv + v);
+    }
+#pragma unroll
+    for (int q = 0; q < kSmallVecs; q++) acc4(x[q], 4 * (q * B + threadIdx.x), acc[0], acc[1]);
+    if (mine) acc4(t, 4 * nvec, acc[0], acc[1]);
+    block_sum<B, 2>(acc, lds, parity);
+    parity ^= 1;
+    if (threadIdx.x == 0) sums[r.c] = fr_chunk_sum{acc[0], acc[1]};
+  }
+}
+
+// flags[c] <- whether chunk c differs; with kSums also both arenas' sums.
+template <int B, bool kSums>
+__global__ __launch_bounds__(B) void k_verify_chunk(const SrcUnit* __restrict__ units, u64 n,
+                                                    const uint8_t* __restrict__ a,
+                                                    const uint8_t* __restrict__ b,
+                                                    uint32_t* __restrict__ flags,
+                                                    fr_chunk_sum* __restrict__ sums_a,
+                                                    fr_chunk_sum* __restrict__ sums_b,
+                                                    u64* __restrict__ zero_word) {
+  constexpr int K = kSums ? 5 : 1;
+  __shared__ u64 lds[2][B / 64][K];
+  int parity = 0;
+  for (u64 g = blockIdx.x; g < n; g += gridDim.x) {
+    const SrcUnit r = units[g];
+    const uint32_t nvec = r.len >> 4, tail = r.len & 15;
+    const uint8_t *pa = a + r.src_off, *pb = b + r.src_off;
+    u32x4 xa[kSmallVecs], xb[kSmallVecs];
+    load_chunk<B>(xa, make_rsrc(pa, 16 * nvec));
+    load_chunk<B>(xb, make_rsrc(pb, 16 * nvec));
+    u32x4 ta = u32x4{0, 0, 0, 0}, tb = ta;
+    if (tail && threadIdx.x == nvec % B) {
+      ta = load_tail(pa + 16 * nvec, tail);
+      tb = load_tail(pb + 16 * nvec, tail);
+    }
+    u64 acc[K] = {};
+    u32x4 d = ta ^ tb;
+#pragma unroll
+    for (int q = 0; q < kSmallVecs; q++) {
+      d |= xa[q] ^ xb[q];
+      if constexpr (kSums) {
+        acc4(xa[q], 4 * (q * B + threadIdx.x), acc[0], acc[1]);
+        acc4(xb[q], 4 * (q * B + threadIdx.x), acc[2], acc[3]);
+      }
+    }
+    if constexpr (kSums) {
+      acc4(ta, 4 * nvec, acc[0], acc[1]);
+      acc4(tb, 4 * nvec, acc[2], acc[3]);
+    }
+    acc[K - 1] = (d.x | d.y | d.z | d.w) != 0;  // lanes that differ
+    block_sum<B, K>(acc, lds, parity);
+    parity ^= 1;
+    if (threadIdx.x == 0) {
+      flags[r.c] = acc[K - 1] != 0;
+      if constexpr (kSums) {
+        sums_a[r.c] = fr_chunk_sum{acc[0], acc[1]};
+        sums_b[r.c] = fr_chunk_sum{acc[2], acc[3]};
+      }
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0;  // last, as in k_unpack
+}
+
+__device__ __forceinline__ uint32_t differs(const fr_chunk_sum& sent, u64 s, u64 ws) {
+  return sent.sum != s || sent.wsum != ws;
+}
+
+// Workgroups [0, n_derived) take a derived group each (its two master chunks
+// and the parameter chunk rounded from them: the longest first), the next
+// n_plain a plain chunk; flags[c] <- whether chunk c's sums, as written,
+// differ from those sent.
+template <int B>
+__global__ __launch_bounds__(B) void k_unpack_chunk(const DerivedUnit* __restrict__ derived, u64 n_derived,
+                                                    const PlainUnit* __restrict__ plain, u64 n_plain,
+                                                    uint32_t cvec, const uint8_t* __restrict__ payload,
+                                                    uint8_t* __restrict__ dst,
+                                                    const fr_chunk_sum* __restrict__ sent,
+                                                    uint32_t* __restrict__ flags,
+                                                    u64* __restrict__ zero_word) {
+  __shared__ u64 lds[2][B / 64][6];
+  __shared__ u64 lds2[2][B / 64][2];
+  int parity = 0;
+  for (u64 g = blockIdx.x; g < n_derived + n_plain; g += gridDim.x) {
+    if (g < n_derived) {
+      const DerivedUnit r = derived[g];
+      const uint32_t mvec = (2 * r.len) >> 4, mtail = (2 * r.len) & 15;  // as in derived_slice
+      const bool two = 2 * r.len > 16 * cvec;  // more than one master chunk
+      const fr_chunk_sum s0 = sent[r.m0], s1 = sent[r.m0 + (two ? 1 : 0)], sp = sent[r.c];
+      const uint8_t* m = payload + r.m_pay_off;
+      const rsrc_t in = make_rsrc(m, 16 * mvec), out = make_rsrc(dst + r.m_dst_off, 16 * mvec),
+                   pout = make_rsrc(dst + r.p_dst_off, 8 * mvec);
+      u32x4 x[2][kSmallVecs];
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int q = 0; q < kSmallVecs; q++) {
+          const uint32_t l = q * B + threadIdx.x;  // a master chunk may be shorter than the threads' vectors
+          x[h][q] = ld_buf(in, l < cvec ? 16 * (h * cvec + l) : kOob);
+        }
+      const bool mine = mtail && threadIdx.x == (mvec & (cvec - 1)) % B;
+      u32x4 t = u32x4{0, 0, 0, 0};
+      if (mine) t = mask_tail(ld_nt(reinterpret_cast<const u32x4*>(m) + mvec), mtail);
+      u64 acc[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int q = 0; q < kSmallVecs; q++) {
+          const uint32_t l = q * B + threadIdx.x, v = h * cvec + l;
+          const bool in_chunk = l < cvec;
+          st_buf(x[h][q], out, in_chunk ? 16 * v : kOob);
+          const u32x2 p = rne4(x[h][q]);
+          st_buf2(p, pout, in_chunk ? 8 * v : kOob);
+          acc4(x[h][q], 4 * l, acc[2 * h], acc[2 * h + 1]);
+          acc2(p, 2 * v, acc[4], acc[5]);  // zeros add nothing (and round to zero)
+        }
+      if (mine) {
+        const uint32_t nf = mtail >> 2;
+        uint32_t* mw = reinterpret_cast<uint32_t*>(dst + r.m_dst_off + 16 * mvec);
+        uint16_t* ph = reinterpret_cast<uint16_t*>(dst + r.p_dst_off + 8 * mvec);
+        const uint32_t h0 = rne_bf16(t.x), h1 = rne_bf16(t.y), h2 = rne_bf16(t.z);
+        mw[0] = t.x;
+        ph[0] = uint16_t(h0);
+        if (nf > 1) {
+          mw[1] = t.y;
+          ph[1] = uint16_t(h1);
+        }
+        if (nf > 2) {
+          mw[2] = t.z;
+          ph[2] = uint16_t(h2);
+        }
+        if (mvec < cvec) acc4(t, 4 * mvec, acc[0], acc[1]);
+        else acc4(t, 4 * (mvec - cvec), acc[2], acc[3]);
+        acc2(u32x2{h0 | (nf > 1 ? h1 << 16 : 0u), nf > 2 ? h2 : 0u}, 2 * mvec, acc[4], acc[5]);
+      }
+      block_sum<B, 6>(acc, lds, parity);
+      parity ^= 1;
+      if (threadIdx.x == 0) {
+        flags[r.m0] = differs(s0, acc[0], acc[1]);
+        if (two) flags[r.m0 + 1] = differs(s1, acc[2], acc[3]);
+        flags[r.c] = differs(sp, acc[4], acc[5]);
+      }
+    } else {
+      const PlainUnit r = plain[g - n_derived];
+      const fr_chunk_sum s0 = sent[r.c];
+      const uint32_t nvec = r.len >> 4, tail = r.len & 15;
+      const uint8_t* s = payload + r.pay_off;
+      const rsrc_t out = make_rsrc(dst + r.dst_off, 16 * nvec);
+      u32x4 x[kSmallVecs];
+      load_chunk<B>(x, make_rsrc(s, 16 * nvec));
+      const bool mine = tail && threadIdx.x == nvec % B;
+      u32x4 t = u32x4{0, 0, 0, 0};
+      if (mine) t = mask_tail(ld_nt(reinterpret_cast<const u32x4*>(s) + nvec), tail);
+      u64 acc[2] = {0, 0};
+#pragma unroll
+      for (int q = 0; q < kSmallVecs; q++) {
+        st_buf(x[q], out, 16 * (q * B + threadIdx.x));
+        acc4(x[q], 4 * (q * B + threadIdx.x), acc[0], acc[1]);
+      }
+      if (mine) {
+        store_tail(dst + r.dst_off + 16 * u64(nvec), t, tail);
+        acc4(t, 4 * nvec, acc[0], acc[1]);
+      }
+      block_sum<B, 2>(acc, lds2, parity);
+      parity ^= 1;
+      if (threadIdx.x == 0) flags[r.c] = differs(s0, acc[0], acc[1]);
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0;  // last, as in k_unpack
 }
 
 // -------------------------------------------------------------- finalize
@@ -1700,7 +1931,7 @@ int verify_impl(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunks,
   const auto* pa = static_cast<const uint8_t*>(a);
   const auto* pb = static_cast<const uint8_t*>(b);
   const dim3 grid(grid_for<B>(wk.n_slices, cfg));
-  if (sums_a && cfg.buf_verify)
+  if (sums_a && cfg.buf_sums)
     hipLaunchKernelGGL((k_verify<B, U, true, true>), grid, dim3(B), 0, st, units, wk, pa, pb,
                        scr.flags, acc_a, acc_b);
   else if (sums_a)
@@ -1726,6 +1957,46 @@ int verify_impl(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunks,
   f.g_shift = wk.g_shift;
   if (f.out) fold_parts(f, wk, slots);
   return launch_finalize(kFlags, f, st, wk.spc_shift);
+}
+
+// One whole chunk per workgroup (small states).
+template <int B>
+int small_impl(const SmallArgs& m, hipStream_t st) {
+  const dim3 block(B);
+  const auto* s = static_cast<const uint8_t*>(m.src);
+  if (m.op == SmallArgs::kPack || m.op == SmallArgs::kChecksum) {
+    const dim3 grid(grid_for<B>(m.n_chunks, m.cfg));
+    auto* p = static_cast<uint8_t*>(m.payload);
+    if (m.op == SmallArgs::kPack)
+      hipLaunchKernelGGL((k_pack_chunk<B, true>), grid, block, 0, st, m.units, u64(m.n_chunks), s, p, m.sums);
+    else
+      hipLaunchKernelGGL((k_pack_chunk<B, false>), grid, block, 0, st, m.units, u64(m.n_chunks), s, p, m.sums);
+    return int(hipGetLastError());
+  }
+  u64* count = reinterpret_cast<u64*>(m.count);
+  if (m.op == SmallArgs::kUnpack) {
+    const dim3 grid(grid_for<B>(u64(m.n_derived) + m.n_plain, m.cfg));
+    hipLaunchKernelGGL((k_unpack_chunk<B>), grid, block, 0, st, m.derived, u64(m.n_derived), m.plain,
+                       u64(m.n_plain), uint32_t(m.C >> 4), s, static_cast<uint8_t*>(m.dst), m.sent,
+                       m.flags, count);
+  } else {
+    const dim3 grid(grid_for<B>(m.n_chunks, m.cfg));
+    const auto* b = static_cast<const uint8_t*>(m.src_b);
+    if (m.sums)
+      hipLaunchKernelGGL((k_verify_chunk<B, true>), grid, block, 0, st, m.units, u64(m.n_chunks), s, b,
+                         m.flags, m.sums, m.sums_b, count);
+    else
+      hipLaunchKernelGGL((k_verify_chunk<B, false>), grid, block, 0, st, m.units, u64(m.n_chunks), s, b,
+                         m.flags, m.sums, m.sums_b, count);
+  }
+  const int e = int(hipGetLastError());
+  if (e) return e;
+  FinalArgs f{};
+  f.flags = m.flags;
+  f.bitmap = m.bitmap;
+  f.count = count;
+  f.n_chunks = m.n_chunks;
+  return launch_finalize(kFlags, f, st);
 }
 
 #define FR_DISPATCH(tile, fn, ...)                        \
@@ -1903,6 +2174,20 @@ int launch_compare_sums(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n
   f.n_chunks = n_chunks;
   f.g_shift = 0;
   return launch_finalize(kCompare, f, st);
+}
+
+int launch_small(const SmallArgs& m, void* stream) {
+  const hipStream_t st = hipStream_t(stream);
+  if (m.n_chunks == 0) {
+    Zeroes z;
+    z.add(m.count, 8);
+    return z.launch(st);
+  }
+  if (m.C <= 64 * 64) return small_impl<64>(m, st);
+  if (m.C <= 128 * 64) return small_impl<128>(m, st);
+  if (m.C <= 256 * 64) return small_impl<256>(m, st);
+  if (m.C <= 512 * 64) return small_impl<512>(m, st);
+  return small_impl<1024>(m, st);
 }
 
 int launch_verify(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunks, uint64_t C,

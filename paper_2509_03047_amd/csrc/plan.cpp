@@ -5,6 +5,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -55,8 +56,11 @@ constexpr int kAlignedLinePack = 2, kAlignedLineUnpack = 1;
 // faster (the block walk that table takes is faster still), unpack 1.5-2.5 %
 // slower, the checksum no faster, and the compare between 0.5 % slower and
 // 1.3 % faster from one box to the next.
+// The compare with sums, whose arithmetic would otherwise stand between its
+// loads, gains 7-15 % (1.4 GB of 1 MiB chunks 460 -> 426 us, tensors at
+// 16-byte offsets 291 -> 255).
 constexpr uint32_t kDefaultBufPack = 0, kDefaultBufUnpack = 0, kDefaultBufVerify = 0,
-                   kDefaultBufChecksum = 0;
+                   kDefaultBufSums = 1, kDefaultBufChecksum = 0;
 // The compare's and the checksum's walks in arena address order instead of
 // chunk order, for tables that list tensors out of arena order: on the
 // descriptor stress table the compare gains 2.8 % (7.19 against 6.99 TB/s)
@@ -184,13 +188,15 @@ static void fill_info(const Layout& L, uint32_t n, uint64_t src, uint64_t dst, i
   info->tile_checksum = uint32_t(cfg.tile_checksum);
 }
 
-static uint32_t env_u32(const char* name, uint32_t dflt) {
+static uint64_t env_u64(const char* name, uint64_t dflt) {
   const char* v = std::getenv(name);
   if (!v || !*v) return dflt;
   char* end = nullptr;
-  unsigned long x = std::strtoul(v, &end, 10);
-  return (end && *end == 0) ? uint32_t(x) : dflt;
+  const unsigned long x = std::strtoul(v, &end, 10);
+  return (end && *end == 0) ? uint64_t(x) : dflt;
 }
+
+static uint32_t env_u32(const char* name, uint32_t dflt) { return uint32_t(env_u64(name, dflt)); }
 
 }  // namespace fr
 
@@ -376,11 +382,69 @@ LaunchCfg launch_config() {
   cfg.buf_pack = int(env_u32("FLASHRESTORE_BUF_PACK", kDefaultBufPack) != 0);
   cfg.buf_unpack = int(env_u32("FLASHRESTORE_BUF_UNPACK", kDefaultBufUnpack) != 0);
   cfg.buf_verify = int(env_u32("FLASHRESTORE_BUF_VERIFY", kDefaultBufVerify) != 0);
+  cfg.buf_sums = int(env_u32("FLASHRESTORE_BUF_VERIFY", kDefaultBufSums) != 0);
   cfg.buf_checksum = int(env_u32("FLASHRESTORE_BUF_CHECKSUM", kDefaultBufChecksum) != 0);
   cfg.order_verify = int(env_u32("FLASHRESTORE_ORDER_VERIFY", kDefaultOrderVerify) != 0);
   cfg.order_checksum = int(env_u32("FLASHRESTORE_ORDER_CHECKSUM", kDefaultOrderChecksum) != 0);
   cfg.line_checksum = lpick("FLASHRESTORE_LINE_CHECKSUM", kDefaultLineChecksum, 0x2);
   return cfg;
+}
+
+// The operations that take one whole chunk per workgroup (kSmall*): those of
+// states small enough that launches and the dependent loads before the data
+// decide, and those whose walks cope badly with the chunk size.  A variable
+// that chooses a tile, a walk, an order or a kind of load turns it off (those
+// choose among the other kernels); FLASHRESTORE_SMALL gives one limit in
+// bytes of state for all operations instead of the rule below.  The lines
+// stand where the two change places in a sweep of states of 3 MB to 14 GB, of
+// aligned tensors and of tensors at 16-byte offsets, in chunks of 64 bytes to
+// 64 KiB (us, walk -> whole chunks):
+//   pack      1 KiB and more: 44 MB of 64 KiB chunks 20.0 -> 15.8, 276 MB
+//             84.6 -> 80.1, but 4 GB of 16 KiB chunks 1,171 -> 1,255; smaller
+//             chunks gain only in the smallest states (3 MB of 64-byte chunks
+//             59 -> 18; 121 MB of 256-byte chunks 155 -> 180)
+//   unpack    44 MB 19.7 -> 18.3, 276 MB 86.0 -> 89.2; at 16-byte offsets
+//             chunks of 2 and 4 KiB gain longer (770 MB 295 -> 279) and
+//             64 KiB chunks that are mostly short lose (37 MB 19.7 -> 22.6);
+//             256-byte chunks 61 -> 73
+//   compare   like unpack (44 MB 17.6 -> 16.0, 238 MB 71.4 -> 73.2); at 16-byte
+//             offsets its line-cut walk gives chunks up to 4 KiB two slices:
+//             2.3 GB of 4 KiB chunks 793 -> 732, of 256-byte ones 4,121 -> 2,824
+//   with sums at 16-byte offsets the same holds up to 32 KiB chunks at any size
+//             (7.6 GB of 4 KiB chunks 3,644 -> 2,683, of 32 KiB ones 2,480 ->
+//             2,403, of 64 KiB ones 2,365 -> 2,502); aligned, 2 KiB chunks (14 GB
+//             6,079 -> 4,537) and small states (44 MB 22.7 -> 20.0; 276 MB of
+//             64 KiB chunks 90.6 -> 94.6)
+//   checksum  chunks up to 2 KiB leave most of a slice's lanes idle (1.4 GB of
+//             1 KiB chunks 431 -> 372); larger: 276 MB of 64 KiB chunks
+//             44.3 -> 41.4, 1.4 GB of 16 KiB chunks 202 -> 211
+uint32_t small_ops(const fr_plan* p) {
+  static const char* const kOptions[] = {"TILE", "LINE", "ABSORB", "BUF", "ORDER"};
+  static const char* const kOps[] = {"", "_PACK", "_UNPACK", "_VERIFY", "_CHECKSUM"};
+  char name[64];
+  for (const char* o : kOptions)
+    for (const char* op : kOps) {
+      std::snprintf(name, sizeof name, "FLASHRESTORE_%s%s", o, op);
+      const char* v = std::getenv(name);
+      if (v && *v) return 0;
+    }
+  const Layout& L = p->layout;
+  const uint64_t C = L.C, state = L.state_bytes, MiB = uint64_t(1) << 20;
+  if (C > kSmallChunk) return 0;
+  const uint64_t limit = env_u64("FLASHRESTORE_SMALL", ~uint64_t(0));
+  if (limit != ~uint64_t(0)) return state <= limit ? kSmallAll : 0;
+  const bool src_lines = p->src_align >= kLine, dst_lines = p->dst_align >= kLine;
+  const bool filled = C <= 16384 || 2 * state >= L.n_chunks * C;  // chunks mostly whole
+  const uint64_t most = filled ? 64 * MiB : 8 * MiB;
+  uint32_t ops = 0;
+  if (state <= (C >= 1024 ? 512 : 8) * MiB) ops |= kSmallPack;
+  if (C >= 2048 && state <= (C <= 4096 && !dst_lines ? 1024 * MiB : most)) ops |= kSmallUnpack;
+  if (C >= 2048 && state <= most) ops |= kSmallVerify;
+  if (C >= 256 && C <= 4096 && !src_lines) ops |= kSmallVerify;
+  if (src_lines ? C == 2048 || (C > 2048 && state <= most) : C >= 256 && (C <= 32768 || state <= most))
+    ops |= kSmallVerifySums;
+  if (C <= 2048 || state <= 320 * MiB) ops |= kSmallChecksum;
+  return ops;
 }
 
 }  // namespace
@@ -517,16 +581,20 @@ int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st) 
   struct Want {
     int tile, line, absorb;
     bool arena;
+    uint32_t small;  // not built where all of these operations take whole chunks
   };
   for (uint64_t c = 1; c < units.size(); c++)
     p->chunks_in_arena_order = p->chunks_in_arena_order && units[c - 1].src_off <= units[c].src_off;
   const Want walks[] = {
-      {p->cfg.tile_pack, p->cfg.line_pack, p->cfg.absorb_pack, false},
-      {p->cfg.tile_checksum, p->cfg.line_checksum, p->cfg.absorb_checksum, p->cfg.order_checksum != 0},
-      {p->cfg.tile_verify, p->cfg.line_verify, p->cfg.absorb_verify, p->cfg.order_verify != 0}};
+      {p->cfg.tile_pack, p->cfg.line_pack, p->cfg.absorb_pack, false, kSmallPack},
+      {p->cfg.tile_checksum, p->cfg.line_checksum, p->cfg.absorb_checksum, p->cfg.order_checksum != 0,
+       kSmallChecksum},
+      {p->cfg.tile_verify, p->cfg.line_verify, p->cfg.absorb_verify, p->cfg.order_verify != 0,
+       kSmallVerify | kSmallVerifySums}};
   std::vector<uint32_t> by_addr;
   for (const Want& tw : walks) {
     if (&tw == &walks[0] && p->cfg.line_pack == kLineBlocks) continue;  // build_pack_blocks
+    if ((p->cfg.small & tw.small) == tw.small) continue;
     const uint32_t sl = slice_bytes(L.C, tw.tile);
     const uint32_t shift = line_walk(p, tw.tile, tw.line);
     const uint32_t absorb = shift && tw.absorb ? 1u : 0u;
@@ -776,7 +844,7 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
                                                               (nc - L.n_sent_chunks) * sizeof(DerivedUnit)));
   const uint64_t b_agg = up(nb * sizeof(DeltaAgg)), b_pre = up(nb * sizeof(DeltaPre));
   const uint64_t b_counts = 256, b_bits = up(nw * 4), b_ids = up(nc * 4), b_payof = up(nc * 8);
-  const uint64_t b_parts = up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
+  const uint64_t b_parts = p->cfg.small == kSmallAll ? 0 : up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
   const uint64_t total =
       b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids + b_parts;
   int rc = upload(nullptr, total, &p->d_delta, st.s);
@@ -877,6 +945,7 @@ extern "C" int fr_plan_create_ex(const fr_tensor_desc* table, uint32_t n, uint64
     };
     p->cfg.line_pack = resolve(p->cfg.line_pack, p->pay_align, kAlignedLinePack);
     p->cfg.line_unpack = resolve(p->cfg.line_unpack, p->dst_align, kAlignedLineUnpack);
+    p->cfg.small = small_ops(p);
 
     Staging st;
     const hipError_t es = hipStreamCreateWithFlags(&st.s, hipStreamNonBlocking);
@@ -893,10 +962,13 @@ extern "C" int fr_plan_create_ex(const fr_tensor_desc* table, uint32_t n, uint64
                   st.s);
     if (rc == FR_OK)
       rc = upload(plain.data(), plain.size() * sizeof(PlainUnit), (void**)&p->d_plain, st.s);
+    // operations that take whole chunks need no walks
+    const uint32_t small = p->cfg.small;
+    const bool pack_tiles = p->cfg.line_pack == kLineBlocks, unpack_tiles = p->cfg.line_unpack == kLineBlocks;
     if (rc == FR_OK) rc = build_src_walks(p, units, st);
-    if (rc == FR_OK && p->cfg.line_pack == kLineBlocks) rc = build_pack_blocks(p, units, st);
-    if (rc == FR_OK && p->cfg.line_unpack != kLineBlocks) rc = build_unpack_walk(p, recs, is_master, st);
-    if (rc == FR_OK && p->cfg.line_unpack == kLineBlocks) rc = build_unpack_blocks(p, recs, is_master, st);
+    if (rc == FR_OK && pack_tiles && !(small & kSmallPack)) rc = build_pack_blocks(p, units, st);
+    if (rc == FR_OK && !unpack_tiles && !(small & kSmallUnpack)) rc = build_unpack_walk(p, recs, is_master, st);
+    if (rc == FR_OK && unpack_tiles && !(small & kSmallUnpack)) rc = build_unpack_blocks(p, recs, is_master, st);
     if (rc == FR_OK) rc = build_scratch(p, st);
     if (rc != FR_OK) {
       fr_plan_destroy(p);
