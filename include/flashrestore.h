@@ -361,8 +361,8 @@ int fr_checksum_state(const fr_plan* plan, const void* base, fr_chunk_sum* sums,
  * set bits in increasing order), for example fr_verify_replicas's output, so
  * that a repair needs no host round trip.  Either way the device builds the
  * list's layout and unit records itself, in memory the plan allocated at
- * creation: no delta call allocates.  A host list is first copied to the
- * device on `stream` through pinned staging the plan owns (the call waits
+ * creation: no delta call allocates.  A host list (of other than consecutive
+ * ids, which need no copy) is first copied to the device on `stream` through pinned staging the plan owns (the call waits
  * until the previous copy from that staging has completed before refilling
  * it), so the host-list calls are not for graph capture; the flagged calls
  * enqueue kernel launches only and may be captured. */

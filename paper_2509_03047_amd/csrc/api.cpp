@@ -415,14 +415,35 @@ int upload_list(const fr_plan* plan, const uint32_t* ids, uint64_t n_ids, hipStr
   return launch_result(launch_ids_to_bits(plan->d_delta_ids, n_ids, plan->d_delta_bits, words, stream));
 }
 
+// A delta call's list: chunks [c0, c1) where bits is NULL (a host list of
+// consecutive ids, which needs no upload), else the bitmap's.  `bound` is its
+// longest possible length, its length where `exact`.
+struct ChunkList {
+  const uint32_t* bits;
+  uint64_t c0, c1, bound;
+  bool exact;
+};
+
+// The bitmap of a host list, uploaded, or the range of one of consecutive ids.
+int host_list(const fr_plan* plan, const uint32_t* ids, uint64_t n_ids, hipStream_t stream,
+              ChunkList* out) {
+  if (uint64_t(ids[n_ids - 1]) - ids[0] + 1 == n_ids) {
+    *out = ChunkList{nullptr, ids[0], ids[0] + n_ids, n_ids, true};
+    return FR_OK;
+  }
+  *out = ChunkList{plan->d_delta_bits, 0, plan->layout.n_chunks, n_ids, true};
+  return upload_list(plan, ids, n_ids, stream);
+}
+
 // Arguments of the list builder for a call of operation `tile` (whose
 // accumulators per list position it clears, with *zero_word if given).
-DeltaBuild delta_build(const fr_plan* plan, const uint32_t* bits, uint64_t* user_counts,
+DeltaBuild delta_build(const fr_plan* plan, const ChunkList& list, uint64_t* user_counts,
                        uint64_t payload_limit, int tile, uint64_t* zero_word) {
   DeltaBuild b{};
   b.loc = plan->d_delta_loc;
-  b.bits = bits;
-  b.n_chunks = plan->layout.n_chunks;
+  b.bits = list.bits;
+  b.c0 = list.c0;
+  b.n_chunks = list.c1;
   b.seg = plan->layout.seg;
   b.agg = plan->d_delta_agg;
   b.pre = plan->d_delta_pre;
@@ -435,7 +456,8 @@ DeltaBuild delta_build(const fr_plan* plan, const uint32_t* bits, uint64_t* user
   b.pay_of = plan->d_delta_payof;
   b.m0 = plan->d_delta_m0;
   b.payload_limit = payload_limit;
-  b.acc = plan->scratch.acc;
+  // whole chunks per workgroup keep no accumulators
+  b.acc = plan->cfg.small & kSmallLists ? nullptr : plan->scratch.acc;
   uint32_t g = 0;
   while ((uint64_t(1) << g) < accumulators_per_chunk(plan->layout.C, tile)) g++;
   b.acc_shift = g;
@@ -443,33 +465,72 @@ DeltaBuild delta_build(const fr_plan* plan, const uint32_t* bits, uint64_t* user
   return b;
 }
 
-// The device half of a delta pack: build the list's records from `bits`,
-// then pack them (at most `bound` units).
-int pack_list(const fr_plan* plan, const void* src_base, const uint32_t* bits, uint64_t bound,
-              void* payload, uint64_t payload_cap, fr_chunk_sum* sums, uint64_t* user_counts,
-              hipStream_t stream) {
-  FR_TRY(launch_result(launch_delta_build(
-      delta_build(plan, bits, user_counts, payload_cap, plan->cfg.tile_pack, nullptr), true, stream)));
-  const uint64_t C = plan->layout.C;
-  return launch_result(launch_pack(plan->d_delta_src,
-                                   list_walk(bound, plan->d_delta_counts + kDeltaIds, C,
-                                             plan->cfg.tile_pack, false),
-                                   uint32_t(bound), C, src_base, payload, sums, plan->scratch,
-                                   plan->cfg, stream));
+// The launch configuration of a pack over a list: a list whose length the
+// host knows needs no cap on its workgroups.
+LaunchCfg list_config(const fr_plan* plan, const ChunkList& list) {
+  LaunchCfg cfg = plan->cfg;
+  if (list.exact) cfg.delta_grid = 0;
+  return cfg;
 }
 
-// The device half of a delta unpack: build the list's records from `bits`,
-// write the sent chunks and re-derive the listed parameters (from re-sent
-// masters in the payload, else from the receiver's own) in one launch,
-// check every listed chunk (at most `bound`).
+// The device half of a delta pack: build the list's records, then pack them.
+int pack_list(const fr_plan* plan, const void* src_base, const ChunkList& list, void* payload,
+              uint64_t payload_cap, fr_chunk_sum* sums, uint64_t* user_counts, hipStream_t stream) {
+  FR_TRY(launch_result(launch_delta_build(
+      delta_build(plan, list, user_counts, payload_cap, plan->cfg.tile_pack, nullptr), true, stream)));
+  const uint64_t C = plan->layout.C;
+  if (list.bound && plan->cfg.small & kSmallLists) {
+    SmallArgs m = small_args(plan, SmallArgs::kPack);
+    m.units = plan->d_delta_src;
+    m.n_chunks = uint32_t(list.bound);
+    m.src = src_base;
+    m.payload = payload;
+    m.sums = sums;
+    m.list_counts = plan->d_delta_counts;
+    m.exact = list.exact;
+    return launch_result(launch_small(m, stream));
+  }
+  return launch_result(launch_pack(plan->d_delta_src,
+                                   list_walk(list.bound, plan->d_delta_counts + kDeltaIds, C,
+                                             plan->cfg.tile_pack, false),
+                                   uint32_t(list.bound), C, src_base, payload, sums, plan->scratch,
+                                   list_config(plan, list), stream));
+}
+
+// The device half of a delta unpack: build the list's records, write the
+// sent chunks and re-derive the listed parameters (from re-sent masters in
+// the payload, else from the receiver's own) in one launch, check every
+// listed chunk.
 int unpack_list(const fr_plan* plan, const void* payload, uint64_t payload_bytes,
-                const fr_chunk_sum* sums, const uint32_t* bits, uint64_t bound, void* dst_base,
-                uint32_t* bad_bitmap, uint64_t* n_bad, hipStream_t stream) {
+                const fr_chunk_sum* sums, const ChunkList& list, void* dst_base, uint32_t* bad_bitmap,
+                uint64_t* n_bad, hipStream_t stream) {
+  const uint64_t bound = list.bound;
+  const bool whole = bound && plan->cfg.small & kSmallLists;
   if (bound) {
     FR_TRY(launch_result(launch_delta_build(
-        delta_build(plan, bits, nullptr, payload_bytes, plan->cfg.tile_unpack, n_bad), false, stream)));
+        delta_build(plan, list, nullptr, payload_bytes, plan->cfg.tile_unpack, n_bad), false, stream)));
   }
   const uint64_t C = plan->layout.C;
+  if (whole) {
+    SmallArgs m = small_args(plan, SmallArgs::kUnpackList);
+    m.n_chunks = uint32_t(bound);
+    m.plain = plan->d_delta_plain;
+    m.derived = plan->d_delta_derived;
+    m.src = payload;
+    m.dst = dst_base;
+    m.sent = sums;
+    m.bitmap = bad_bitmap;
+    m.count = n_bad;
+    m.list_counts = plan->d_delta_counts;
+    m.exact = list.exact;
+    m.bad = plan->scratch.flags;
+    m.bits = list.bits;
+    m.c0 = list.c0;
+    m.c1 = list.c1;
+    m.pay_of = plan->d_delta_payof;
+    m.flags = plan->d_delta_flags;
+    return launch_result(launch_small(m, stream));
+  }
   UnpackDeltaArgs a{};
   a.plain = plan->d_delta_plain;
   a.n_plain = 0;
@@ -489,9 +550,11 @@ int unpack_list(const fr_plan* plan, const void* payload, uint64_t payload_bytes
     a.live = plan->d_delta_counts + kDeltaIds;
     a.bad = plan->scratch.flags;
   }
-  a.bits = bits;
+  a.bits = list.bits;
+  a.c0 = list.c0;
+  a.c1 = list.c1;
   a.pay_of = plan->d_delta_payof;
-  return launch_result(launch_unpack_delta(a, plan->cfg, stream));
+  return launch_result(launch_unpack_delta(a, list_config(plan, list), stream));
 }
 
 }  // namespace
@@ -519,8 +582,9 @@ extern "C" int fr_pack_chunks(const fr_plan* plan, const void* src_base, const u
   const Region ins[] = {{src_base, plan->src_arena_bytes}};
   FR_TRY(check_disjoint(outs, 2, ins, 1));
   if (n_ids == 0) return FR_OK;
-  FR_TRY(upload_list(plan, ids, n_ids, stream));
-  return pack_list(plan, src_base, plan->d_delta_bits, n_ids, payload, pb, sums, nullptr, stream);
+  ChunkList list{};
+  FR_TRY(host_list(plan, ids, n_ids, stream, &list));
+  return pack_list(plan, src_base, list, payload, pb, sums, nullptr, stream);
 }
 
 extern "C" int fr_unpack_chunks(const fr_plan* plan, const void* payload, uint64_t payload_bytes,
@@ -541,9 +605,9 @@ extern "C" int fr_unpack_chunks(const fr_plan* plan, const void* payload, uint64
   const Region outs[] = {{dst_base, plan->dst_arena_bytes}, {bad_bitmap, words * 4}, {n_bad, 8}};
   const Region ins[] = {{payload, pb}, {sums, n_ids * sizeof(fr_chunk_sum)}};
   FR_TRY(check_disjoint(outs, 3, ins, 2));
-  if (n_ids) FR_TRY(upload_list(plan, ids, n_ids, stream));
-  return unpack_list(plan, payload, pb, sums, plan->d_delta_bits, n_ids, dst_base, bad_bitmap,
-                     n_bad, stream);
+  ChunkList list{};
+  if (n_ids) FR_TRY(host_list(plan, ids, n_ids, stream, &list));
+  return unpack_list(plan, payload, pb, sums, list, dst_base, bad_bitmap, n_bad, stream);
 }
 
 extern "C" int fr_pack_flagged(const fr_plan* plan, const void* src_base, const uint32_t* flagged,
@@ -562,7 +626,8 @@ extern "C" int fr_pack_flagged(const fr_plan* plan, const void* src_base, const 
   const Region outs[] = {{payload, pmax}, {sums, L.n_chunks * sizeof(fr_chunk_sum)}, {counts, counts ? 16u : 0u}};
   const Region ins[] = {{src_base, plan->src_arena_bytes}, {flagged, words * 4}};
   FR_TRY(check_disjoint(outs, 3, ins, 2));
-  return pack_list(plan, src_base, flagged, L.n_chunks, payload, pmax, sums, counts, stream);
+  return pack_list(plan, src_base, ChunkList{flagged, 0, L.n_chunks, L.n_chunks, false}, payload, pmax,
+                   sums, counts, stream);
 }
 
 extern "C" int fr_unpack_flagged(const fr_plan* plan, const void* payload, uint64_t payload_bytes,
@@ -582,8 +647,8 @@ extern "C" int fr_unpack_flagged(const fr_plan* plan, const void* payload, uint6
   const Region ins[] = {{payload, payload_bytes}, {sums, L.n_chunks * sizeof(fr_chunk_sum)},
                         {flagged, words * 4}};
   FR_TRY(check_disjoint(outs, 3, ins, 3));
-  return unpack_list(plan, payload, payload_bytes, sums, flagged, L.n_chunks, dst_base, bad_bitmap,
-                     n_bad, stream);
+  return unpack_list(plan, payload, payload_bytes, sums, ChunkList{flagged, 0, L.n_chunks, L.n_chunks, false},
+                     dst_base, bad_bitmap, n_bad, stream);
 }
 
 extern "C" const char* fr_strerror(int status) {

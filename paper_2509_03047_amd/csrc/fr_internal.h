@@ -193,6 +193,7 @@ struct LaunchCfg {
 };
 constexpr uint32_t kSmallPack = 1, kSmallUnpack = 2, kSmallVerify = 4, kSmallVerifySums = 8,
                    kSmallChecksum = 16, kSmallAll = 31;
+constexpr uint32_t kSmallLists = 32;  // the delta calls' listed chunks
 
 // Device scratch owned by a plan: partial sums, one place per slot of the
 // longest walk (the delta calls use the same memory as G accumulators per
@@ -244,6 +245,7 @@ struct UnpackDeltaArgs {
   // payload offset (DeltaBuild::pay_of): a derived chunk reads a master
   // chunk from the payload when it was re-sent, else from the receiver
   const uint32_t* bits = nullptr;
+  uint64_t c0 = 0, c1 = 0;  // bits NULL: chunks [c0, c1) are listed
   const uint64_t* pay_of = nullptr;
 };
 
@@ -280,8 +282,9 @@ constexpr uint32_t kListBlock = 256;
 
 struct DeltaBuild {
   const ChunkLoc* loc;       // per chunk id
-  const uint32_t* bits;      // the list: bit c set = chunk c listed
-  uint64_t n_chunks;         // the plan's chunks (bits past them are ignored)
+  const uint32_t* bits;      // the list: bit c set = chunk c listed; NULL: chunks [c0, n_chunks)
+  uint64_t c0;               // the first chunk id looked at (0 with bits)
+  uint64_t n_chunks;         // the plan's chunks (bits past them are ignored); NULL bits: the list's end
   uint64_t seg;              // payload segment alignment A
   DeltaAgg* agg;             // per block of kListBlock chunks
   DeltaPre* pre;             // per block
@@ -295,7 +298,7 @@ struct DeltaBuild {
                              //   (kNoPayload if beyond the readable payload)
   const uint32_t* m0;        // per chunk id: a derived chunk's first master chunk
   uint64_t payload_limit;    // pack: payload capacity; unpack: readable payload bytes
-  fr_chunk_sum* acc;         // accumulators of the operation, cleared per listed position
+  fr_chunk_sum* acc;         // accumulators of the operation, cleared per listed position, or NULL
   uint32_t acc_shift;        // log2 of the accumulators per list position
   uint64_t* zero_word;       // NULL, or a counter the operation starts from 0 (n_bad)
 };
@@ -357,7 +360,7 @@ struct UnpackBlocks {
 // chunk a workgroup of 1024 threads holds (four 16-byte vectors a thread).
 constexpr uint64_t kSmallChunk = uint64_t(1) << 16;
 struct SmallArgs {
-  enum Op { kPack, kChecksum, kVerify, kUnpack } op = kPack;
+  enum Op { kPack, kChecksum, kVerify, kUnpack, kUnpackList } op = kPack;
   LaunchCfg cfg;
   uint64_t C = 0;
   uint32_t n_chunks = 0;
@@ -375,6 +378,17 @@ struct SmallArgs {
   uint32_t* flags = nullptr;  // one per chunk (scratch)
   uint32_t* bitmap = nullptr;
   uint64_t* count = nullptr;
+  // Lists built on the device.  n_chunks is the list's longest possible
+  // length, or with `exact` its length; counts the device's (DeltaCount).
+  // kUnpackList: plain and derived as k_list_build writes them, `bad` per
+  // list position; the list itself (bits, or chunks [c0, c1)) and each listed
+  // sent chunk's payload offset.
+  const uint64_t* list_counts = nullptr;
+  bool exact = false;
+  const uint32_t* bad = nullptr;
+  const uint32_t* bits = nullptr;
+  uint64_t c0 = 0, c1 = 0;
+  const uint64_t* pay_of = nullptr;
 };
 
 // Kernel launchers (kernels.hip).  They assume validated arguments, enqueue
@@ -490,6 +504,7 @@ struct fr_plan {
   uint32_t* d_delta_ids = nullptr;     // a host list, uploaded
   uint64_t* d_delta_payof = nullptr;   // per chunk: payload offset in the last delta unpack
   uint32_t* d_delta_m0 = nullptr;      // per chunk: a derived chunk's first master chunk
+  uint32_t* d_delta_flags = nullptr;   // per list position: failed its check (whole chunks)
   uint32_t* h_delta_ids = nullptr;     // pinned staging of a host list
   hipEvent_t delta_ids_copied = nullptr;  // the last upload from the staging has completed
   fr::Scratch scratch{};

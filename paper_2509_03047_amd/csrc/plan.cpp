@@ -432,11 +432,11 @@ uint32_t small_ops(const fr_plan* p) {
   const uint64_t C = L.C, state = L.state_bytes, MiB = uint64_t(1) << 20;
   if (C > kSmallChunk) return 0;
   const uint64_t limit = env_u64("FLASHRESTORE_SMALL", ~uint64_t(0));
-  if (limit != ~uint64_t(0)) return state <= limit ? kSmallAll : 0;
+  if (limit != ~uint64_t(0)) return state <= limit ? kSmallAll | kSmallLists : 0;
   const bool src_lines = p->src_align >= kLine, dst_lines = p->dst_align >= kLine;
   const bool filled = C <= 16384 || 2 * state >= L.n_chunks * C;  // chunks mostly whole
   const uint64_t most = filled ? 64 * MiB : 8 * MiB;
-  uint32_t ops = 0;
+  uint32_t ops = kSmallLists;
   if (state <= (C >= 1024 ? 512 : 8) * MiB) ops |= kSmallPack;
   if (C >= 2048 && state <= (C <= 4096 && !dst_lines ? 1024 * MiB : most)) ops |= kSmallUnpack;
   if (C >= 2048 && state <= most) ops |= kSmallVerify;
@@ -844,9 +844,9 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
                                                               (nc - L.n_sent_chunks) * sizeof(DerivedUnit)));
   const uint64_t b_agg = up(nb * sizeof(DeltaAgg)), b_pre = up(nb * sizeof(DeltaPre));
   const uint64_t b_counts = 256, b_bits = up(nw * 4), b_ids = up(nc * 4), b_payof = up(nc * 8);
-  const uint64_t b_parts = p->cfg.small == kSmallAll ? 0 : up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
+  const uint64_t b_parts = (p->cfg.small & kSmallAll) == kSmallAll ? 0 : up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
   const uint64_t total =
-      b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids + b_parts;
+      b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + 2 * b_ids + b_parts;
   int rc = upload(nullptr, total, &p->d_delta, st.s);
   if (rc != FR_OK) return rc;
   uint8_t* q = static_cast<uint8_t*>(p->d_delta);
@@ -869,6 +869,7 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
   p->d_delta_ids = reinterpret_cast<uint32_t*>(take(b_ids));
   p->d_delta_payof = reinterpret_cast<uint64_t*>(take(b_payof));
   p->d_delta_m0 = reinterpret_cast<uint32_t*>(take(b_ids));
+  p->d_delta_flags = reinterpret_cast<uint32_t*>(take(b_ids));
   st.parts = reinterpret_cast<ChunkParts*>(take(b_parts));
   std::vector<ChunkLoc> loc(nc);
   std::vector<uint32_t> m0(nc, 0);
