@@ -66,7 +66,8 @@
  *   On any error nothing is enqueued and no output is touched.  A checksum or
  *   compare mismatch is data (a set bit and a count), not an error.
  *   Operations on one plan share the plan's device scratch: they must not run
- *   concurrently (issue them on one stream, or order the streams), and one
+ *   concurrently (issue them on one stream, or order the streams; the
+ *   results of concurrent ones, and of later ones, are undefined), and one
  *   plan must not be used from several host threads at once; use one plan per
  *   concurrent stream.
  *   Graph capture.  The four whole-state operations, fr_compare_sums and

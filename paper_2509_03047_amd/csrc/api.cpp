@@ -118,6 +118,7 @@ SmallArgs small_args(const fr_plan* plan, SmallArgs::Op op) {
   m.n_chunks = uint32_t(plan->layout.n_chunks);
   m.units = plan->d_units;
   m.flags = plan->scratch.flags;
+  m.arrive = plan->d_arrive;
   return m;
 }
 
@@ -241,16 +242,20 @@ int verify_checks(const fr_plan* plan, const void* base_a, const void* base_b,
   return *walk ? FR_OK : FR_E_INVAL;
 }
 
-// The compare by whole chunks, its flags in `flags` (4 bytes per chunk).
+// The compare by whole chunks; `flags` (4 bytes per chunk) for the call that
+// keeps to the static scratch, NULL for the plan's own.
 int verify_small(const fr_plan* plan, const void* a, const void* b, uint32_t* bitmap,
                  uint64_t* n_diff, fr_chunk_sum* sums_a, fr_chunk_sum* sums_b, uint32_t* flags,
                  hipStream_t stream) {
   SmallArgs m = small_args(plan, SmallArgs::kVerify);
+  if (flags) {
+    m.arrive = nullptr;
+    m.flags = flags;
+  }
   m.src = a;
   m.src_b = b;
   m.sums = sums_a;
   m.sums_b = sums_b;
-  m.flags = flags;
   m.bitmap = bitmap;
   m.count = n_diff;
   return launch_result(launch_small(m, stream));
@@ -266,7 +271,7 @@ extern "C" int fr_verify_replicas(const fr_plan* plan, const void* base_a, const
   const Layout& L = plan->layout;
   if (verify_whole(plan, sums_a))
     return verify_small(plan, base_a, base_b, diff_bitmap, n_diff, sums_a, sums_b,
-                        plan->scratch.flags, stream);
+                        nullptr, stream);
   return launch_result(launch_verify(plan->d_units, *walk, uint32_t(L.n_chunks), L.C, base_a,
                                      base_b, diff_bitmap, n_diff, sums_a, sums_b, plan->scratch,
                                      plan->cfg, stream));
@@ -288,7 +293,8 @@ extern "C" int fr_compare_sums(const fr_plan* plan, const fr_chunk_sum* sums_a,
   const Region ins[] = {{sums_a, sb}, {sums_b, sb}};
   FR_TRY(check_disjoint(outs, 2, ins, 2));
   return launch_result(
-      launch_compare_sums(sums_a, sums_b, uint32_t(L.n_chunks), diff_bitmap, n_diff, stream));
+      launch_compare_sums(sums_a, sums_b, uint32_t(L.n_chunks), diff_bitmap, n_diff,
+                          plan->d_sums_arrive, stream));
 }
 
 extern "C" int fr_verify_replicas_noalloc(const fr_plan* plan, const void* base_a,
@@ -528,7 +534,6 @@ int unpack_list(const fr_plan* plan, const void* payload, uint64_t payload_bytes
     m.c0 = list.c0;
     m.c1 = list.c1;
     m.pay_of = plan->d_delta_payof;
-    m.flags = plan->d_delta_flags;
     return launch_result(launch_small(m, stream));
   }
   UnpackDeltaArgs a{};

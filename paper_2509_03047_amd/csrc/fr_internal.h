@@ -359,6 +359,13 @@ struct UnpackBlocks {
 // An operation of a small state, one whole chunk per workgroup: the largest
 // chunk a workgroup of 1024 threads holds (four 16-byte vectors a thread).
 constexpr uint64_t kSmallChunk = uint64_t(1) << 16;
+constexpr uint64_t kArriveLine = 128, kArriveGroup = 64;
+// Bytes of the arrival lines for n chunks: one for all, one per bitmap word
+// and one per group of words.
+inline uint64_t arrive_bytes(uint64_t n) {
+  const uint64_t words = (n + 31) / 32;
+  return (1 + words + (words + kArriveGroup - 1) / kArriveGroup) * kArriveLine;
+}
 struct SmallArgs {
   enum Op { kPack, kChecksum, kVerify, kUnpack, kUnpackList } op = kPack;
   LaunchCfg cfg;
@@ -375,7 +382,8 @@ struct SmallArgs {
   const fr_chunk_sum* sent = nullptr;
   fr_chunk_sum* sums = nullptr;  // compare: NULL or the first arena's
   fr_chunk_sum* sums_b = nullptr;
-  uint32_t* flags = nullptr;  // one per chunk (scratch)
+  uint32_t* flags = nullptr;   // one per chunk (scratch)
+  uint64_t* arrive = nullptr;  // the plan's d_arrive (lists: needed), or NULL: flags and a finalize launch
   uint32_t* bitmap = nullptr;
   uint64_t* count = nullptr;
   // Lists built on the device.  n_chunks is the list's longest possible
@@ -421,9 +429,10 @@ int launch_verify(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunk
                   const void* a, const void* b, uint32_t* bitmap, uint64_t* n_diff,
                   fr_chunk_sum* sums_a, fr_chunk_sum* sums_b, const Scratch& scr,
                   const LaunchCfg& cfg, void* stream);
-// Bit c of `bitmap` set iff the two sums of chunk c differ; `count` the bits set.
+// Bit c of `bitmap` set iff the two sums of chunk c differ; `count` the bits set;
+// top: a word of the device that is zero between operations.
 int launch_compare_sums(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
-                        uint32_t* bitmap, uint64_t* count, void* stream);
+                        uint32_t* bitmap, uint64_t* count, uint64_t* top, void* stream);
 // The unit records of a delta list given as a bitmap, built on the device:
 // pack's SrcUnit list, or unpack's plain and derived lists, and the counts;
 // it also clears the accumulators of the listed positions and *zero_word,
@@ -504,7 +513,10 @@ struct fr_plan {
   uint32_t* d_delta_ids = nullptr;     // a host list, uploaded
   uint64_t* d_delta_payof = nullptr;   // per chunk: payload offset in the last delta unpack
   uint32_t* d_delta_m0 = nullptr;      // per chunk: a derived chunk's first master chunk
-  uint32_t* d_delta_flags = nullptr;   // per list position: failed its check (whole chunks)
+  // lines of arrivals and set bits, zero between operations, by which the last
+  // workgroups of a kernel know that they are last (kernels.hip, Finish)
+  uint64_t* d_arrive = nullptr;
+  uint64_t* d_sums_arrive = nullptr;  // the same for the compare of sums, which uses no other scratch
   uint32_t* h_delta_ids = nullptr;     // pinned staging of a host list
   hipEvent_t delta_ids_copied = nullptr;  // the last upload from the staging has completed
   fr::Scratch scratch{};

@@ -845,8 +845,9 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
   const uint64_t b_agg = up(nb * sizeof(DeltaAgg)), b_pre = up(nb * sizeof(DeltaPre));
   const uint64_t b_counts = 256, b_bits = up(nw * 4), b_ids = up(nc * 4), b_payof = up(nc * 8);
   const uint64_t b_parts = (p->cfg.small & kSmallAll) == kSmallAll ? 0 : up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
+  const uint64_t b_arrive = up(arrive_bytes(nc) + kArriveLine);
   const uint64_t total =
-      b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + 2 * b_ids + b_parts;
+      b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids + b_arrive + b_parts;
   int rc = upload(nullptr, total, &p->d_delta, st.s);
   if (rc != FR_OK) return rc;
   uint8_t* q = static_cast<uint8_t*>(p->d_delta);
@@ -869,10 +870,11 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
   p->d_delta_ids = reinterpret_cast<uint32_t*>(take(b_ids));
   p->d_delta_payof = reinterpret_cast<uint64_t*>(take(b_payof));
   p->d_delta_m0 = reinterpret_cast<uint32_t*>(take(b_ids));
-  p->d_delta_flags = reinterpret_cast<uint32_t*>(take(b_ids));
+  p->d_arrive = reinterpret_cast<uint64_t*>(take(b_arrive));
+  p->d_sums_arrive = p->d_arrive + (b_arrive - kArriveLine) / 8;
   st.parts = reinterpret_cast<ChunkParts*>(take(b_parts));
   std::vector<ChunkLoc> loc(nc);
-  std::vector<uint32_t> m0(nc, 0);
+  std::vector<uint32_t> m0((b_ids + b_arrive) / 4, 0);  // and d_arrive's zeros behind them
   for (uint32_t k = 0; k < p->table.size(); k++) {
     const uint64_t c0 = L.chunk_base[k], c1 = L.chunk_base[k + 1];
     for (uint64_t c = c0; c < c1; c++) {
@@ -889,7 +891,7 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
     }
   }
   rc = copy_in(p->d_delta_loc, loc.data(), nc * sizeof(ChunkLoc), st.s);
-  if (rc == FR_OK) rc = copy_in(p->d_delta_m0, m0.data(), nc * sizeof(uint32_t), st.s);
+  if (rc == FR_OK) rc = copy_in(p->d_delta_m0, m0.data(), m0.size() * sizeof(uint32_t), st.s);
   if (rc != FR_OK) return rc;
   hipError_t e = hipSuccess;
   if (nc)
