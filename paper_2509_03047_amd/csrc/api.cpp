@@ -115,6 +115,7 @@ SmallArgs small_args(const fr_plan* plan, SmallArgs::Op op) {
   m.op = op;
   m.cfg = plan->cfg;
   m.C = plan->layout.C;
+  m.longest = plan->layout.longest;
   m.n_chunks = uint32_t(plan->layout.n_chunks);
   m.units = plan->d_units;
   m.flags = plan->scratch.flags;
@@ -293,7 +294,7 @@ extern "C" int fr_compare_sums(const fr_plan* plan, const fr_chunk_sum* sums_a,
   const Region ins[] = {{sums_a, sb}, {sums_b, sb}};
   FR_TRY(check_disjoint(outs, 2, ins, 2));
   return launch_result(
-      launch_compare_sums(sums_a, sums_b, uint32_t(L.n_chunks), diff_bitmap, n_diff,
+      launch_sums_compare(sums_a, sums_b, uint32_t(L.n_chunks), diff_bitmap, n_diff,
                           plan->d_sums_arrive, stream));
 }
 

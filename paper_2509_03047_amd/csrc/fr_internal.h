@@ -159,6 +159,7 @@ struct Layout {
   uint64_t payload_bytes = 0;
   uint64_t state_bytes = 0;
   uint64_t n_sent_chunks = 0;       // chunks of non-derived entries
+  uint64_t longest = 0;             // bytes of the longest chunk
   uint64_t delta_payload_max = 0;   // the largest delta payload any list of chunks can need
   std::vector<uint64_t> pay_off;     // per entry; kNoPayload for derived
   std::vector<uint64_t> chunk_base;  // n_entries + 1
@@ -366,10 +367,17 @@ inline uint64_t arrive_bytes(uint64_t n) {
   const uint64_t words = (n + 31) / 32;
   return (1 + words + (words + kArriveGroup - 1) / kArriveGroup) * kArriveLine;
 }
+// Threads of a workgroup that holds a chunk of `longest` bytes.
+inline uint32_t small_threads(uint64_t longest) {
+  uint32_t b = 64;
+  while (b < 1024 && uint64_t(b) * 64 < longest) b *= 2;
+  return b;
+}
 struct SmallArgs {
   enum Op { kPack, kChecksum, kVerify, kUnpack, kUnpackList } op = kPack;
   LaunchCfg cfg;
   uint64_t C = 0;
+  uint64_t longest = 0;  // bytes of the plan's longest chunk
   uint32_t n_chunks = 0;
   const SrcUnit* units = nullptr;  // pack, checksum, compare: chunk order
   const DerivedUnit* derived = nullptr;
@@ -431,7 +439,7 @@ int launch_verify(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunk
                   const LaunchCfg& cfg, void* stream);
 // Bit c of `bitmap` set iff the two sums of chunk c differ; `count` the bits set;
 // top: a word of the device that is zero between operations.
-int launch_compare_sums(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
+FR_WEAK int launch_sums_compare(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
                         uint32_t* bitmap, uint64_t* count, uint64_t* top, void* stream);
 // The unit records of a delta list given as a bitmap, built on the device:
 // pack's SrcUnit list, or unpack's plain and derived lists, and the counts;

@@ -957,7 +957,9 @@ __global__ __launch_bounds__(B) void k_verify(const SrcUnit* __restrict__ units,
 // through buffer resources, and ends up with the chunk's whole sums.  Pack
 // and the checksum are then one launch, and unpack and the compare leave one
 // flag per chunk to the finalize kernel.  B threads hold kSmallVecs vectors
-// each, B * 64 >= C bytes.
+// each, B * 64 >= the plan's longest chunk (threads for C bytes instead, where
+// 64 KiB chunks hold at most 12 KB: 3,160 of them packed in 32 us, by slices in
+// 21).
 constexpr int kSmallVecs = 4;
 constexpr uint32_t kListWaves = 65536;  // most waves launched over a list of unknown length
 
@@ -2455,7 +2457,7 @@ int launch_unpack_delta(const UnpackDeltaArgs& u, const LaunchCfg& cfg, void* st
   FR_DISPATCH(cfg.tile_unpack, unpack_delta_impl, u, cfg, hipStream_t(stream));
 }
 
-int launch_compare_sums(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
+int launch_sums_compare(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
                         uint32_t* bitmap, uint64_t* count, uint64_t* top, void* stream) {
   // the compare finalize with one accumulator per chunk: the first sums
   // folded (as they are) against the second as the sums sent
@@ -2483,11 +2485,13 @@ int launch_small(const SmallArgs& m, void* stream) {
     z.add(m.count, 8);
     return z.launch(st);
   }
-  if (m.C <= 64 * 64) return small_impl<64>(m, st);
-  if (m.C <= 128 * 64) return small_impl<128>(m, st);
-  if (m.C <= 256 * 64) return small_impl<256>(m, st);
-  if (m.C <= 512 * 64) return small_impl<512>(m, st);
-  return small_impl<1024>(m, st);
+  switch (small_threads(m.longest)) {
+    case 64: return small_impl<64>(m, st);
+    case 128: return small_impl<128>(m, st);
+    case 256: return small_impl<256>(m, st);
+    case 512: return small_impl<512>(m, st);
+    default: return small_impl<1024>(m, st);
+  }
 }
 
 int launch_verify(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunks, uint64_t C,

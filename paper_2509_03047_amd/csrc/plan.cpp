@@ -140,6 +140,7 @@ int validate_and_layout(const fr_tensor_desc* t, uint32_t n, uint64_t C, uint64_
     uint64_t nb = t[k].numel * esize(t[k].dtype);
     L->chunk_base[k] = base;
     base += (nb + C - 1) / C;
+    L->longest = std::max(L->longest, std::min(nb, C));
     if (t[k].derive_from < 0) {
       L->n_sent_chunks += (nb + C - 1) / C;
       sent_bytes += nb;
@@ -429,19 +430,21 @@ uint32_t small_ops(const fr_plan* p) {
       if (v && *v) return 0;
     }
   const Layout& L = p->layout;
-  const uint64_t C = L.C, state = L.state_bytes, MiB = uint64_t(1) << 20;
-  if (C > kSmallChunk) return 0;
+  if (L.longest > kSmallChunk) return 0;
+  // what a workgroup holds, and the chunk size unless no chunk is that long
+  const uint64_t held = 64 * uint64_t(small_threads(L.longest)), C = std::min(L.C, held);
+  const uint64_t state = L.state_bytes, MiB = uint64_t(1) << 20;
   const uint64_t limit = env_u64("FLASHRESTORE_SMALL", ~uint64_t(0));
   if (limit != ~uint64_t(0)) return state <= limit ? kSmallAll | kSmallLists : 0;
   const bool src_lines = p->src_align >= kLine, dst_lines = p->dst_align >= kLine;
-  const bool filled = C <= 16384 || 2 * state >= L.n_chunks * C;  // chunks mostly whole
+  const bool filled = C <= 16384 || 2 * state >= L.n_chunks * held;  // chunks mostly whole
   const uint64_t most = filled ? 64 * MiB : 8 * MiB;
   uint32_t ops = kSmallLists;
-  if (state <= (C >= 1024 ? 512 : 8) * MiB) ops |= kSmallPack;
+  if (state <= (C >= 1024 && filled ? 512 : 8) * MiB) ops |= kSmallPack;
   if (C >= 2048 && state <= (C <= 4096 && !dst_lines ? 1024 * MiB : most)) ops |= kSmallUnpack;
   if (C >= 2048 && state <= most) ops |= kSmallVerify;
   if (C >= 256 && C <= 4096 && !src_lines) ops |= kSmallVerify;
-  if (src_lines ? C == 2048 || (C > 2048 && state <= most) : C >= 256 && (C <= 32768 || state <= most))
+  if (src_lines ? C == 2048 || (C > 2048 && state <= most) : C >= 256 && ((C <= 32768 && filled) || state <= most))
     ops |= kSmallVerifySums;
   if (C <= 2048 || state <= 320 * MiB) ops |= kSmallChecksum;
   return ops;
