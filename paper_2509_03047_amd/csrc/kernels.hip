@@ -1340,8 +1340,8 @@ __global__ __launch_bounds__(B) void k_unpack_list_chunk(
 //   kFlags:   bit c = (flags[c] != 0); optional folds of two
 //             sets into sums_a / sums_b                         (verify)
 // A chunk's sums are either G consecutive accumulators, folded by one lane,
-// or the partial sums at its places (`parts`), folded by kLanes lanes (1, 4
-// or 16, by the slices of a chunk), each with up to kBatch loads in flight.
+// or the partial sums at its places (`parts`), folded by kLanes lanes (1, 4, 16
+// or 32, by the slices of a chunk), each with up to kBatch loads in flight.
 // Measured (51 MB state of 804 chunks of 16 places / 14 GB state of 214,684):
 // 3.9 / 16 us with 16 lanes a chunk, 5.0 / 13 us with one lane and 16 loads
 // in flight, 4.2 / 16 us with 16 lanes and four chunks at once; the large
@@ -1410,19 +1410,22 @@ __device__ __forceinline__ fr_chunk_sum fold(const FinalArgs& f, const fr_chunk_
     s = add_dpp<0x4E>(add_dpp<0xB1>(s));
     ws = add_dpp<0x4E>(add_dpp<0xB1>(ws));
   }
-  if (kLanes == 16) {  // then over the row's quads
+  if (kLanes >= 16) {  // then over the row's quads
     s = add_dpp<0x128>(add_dpp<0x124>(s));
     ws = add_dpp<0x128>(add_dpp<0x124>(ws));
+  }
+  if (kLanes == 32) {  // and the two rows
+    s += __shfl_xor(s, 16, 64);
+    ws += __shfl_xor(ws, 16, 64);
   }
   return fr_chunk_sum{s, ws};
 }
 
-constexpr int kFinalThreads = 1024;
-
-template <int kMode, int kLanes, int kBatch>
-__global__ __launch_bounds__(kFinalThreads) void k_finalize(FinalArgs f) {
-  constexpr uint32_t kChunks = kFinalThreads / kLanes;  // of one pass of a workgroup
-  __shared__ u64 wave_count[kFinalThreads / 64];
+template <int kMode, int kThreads, int kLanes, int kBatch>
+__global__ __launch_bounds__(kThreads) void k_finalize(FinalArgs f) {
+  constexpr uint32_t kChunks = kThreads / kLanes;  // of one pass of a workgroup; with bits whole words
+  static_assert(kMode == kFold || kChunks % 32 == 0, "bitmap words are written whole");
+  __shared__ u64 wave_count[kThreads / 64];
   __shared__ uint8_t group_bit[kChunks];
   const uint32_t lane = threadIdx.x & 63, sub = threadIdx.x % kLanes;
   u64 count = 0;  // set bits seen by this wave (uniform)
@@ -1466,7 +1469,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_finalize(FinalArgs f) {
     const u64 mask = __ballot(bit);
     const u64 w = wbase >> 5;
     if (lane == 0) f.bitmap[w] = uint32_t(mask);
-    if (lane == 32 && wbase + 32 < f.n_chunks) f.bitmap[w + 1] = uint32_t(mask >> 32);
+    if (kChunks > 32 && lane == 32 && wbase + 32 < f.n_chunks) f.bitmap[w + 1] = uint32_t(mask >> 32);
     count += u64(__popcll(mask));
   }
   if (kMode == kFold) return;  // uniform over the grid
@@ -1475,7 +1478,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_finalize(FinalArgs f) {
   if (threadIdx.x == 0) {
     u64 t = 0;
 #pragma unroll
-    for (int i = 0; i < kFinalThreads / 64; i++) t += wave_count[i];
+    for (int i = 0; i < kThreads / 64; i++) t += wave_count[i];
     if (f.top) {
       const u64 add = (t << 32) + 1, all = atomicAdd(f.top, add) + add;
       if (uint32_t(all) == gridDim.x) {
@@ -1962,20 +1965,37 @@ inline void fold_parts(FinalArgs& f, const Walk& wk, const SlotTable& t) {
   f.stride = wk.stride;
 }
 
-template <int kMode, int kLanes, int kBatch>
+template <int kMode, int kLanes, int kBatch, int kThreads = 1024>
 inline int launch_finalize_as(const FinalArgs& f, hipStream_t st) {
-  constexpr u64 per = kFinalThreads / kLanes, most = kLanes == 1 ? 2048 : 32768;
+  constexpr u64 per = kThreads / kLanes, most = kLanes == 1 ? 2048 : 32768;
   const u64 want = (u64(f.n_chunks) + per - 1) / per;
-  const dim3 grid(uint32_t(want < most ? want : most)), block(kFinalThreads);
-  hipLaunchKernelGGL((k_finalize<kMode, kLanes, kBatch>), grid, block, 0, st, f);
+  const dim3 grid(uint32_t(want < most ? want : most)), block(kThreads);
+  hipLaunchKernelGGL((k_finalize<kMode, kThreads, kLanes, kBatch>), grid, block, 0, st, f);
   return int(hipGetLastError());
 }
+
+// A chunk's places lie in eight XCDs' regions, so a wave's loads touch a line
+// for almost every pair of lanes, and few workgroups are bound by what one CU's
+// address unit takes.  So chunks of many places go to smaller workgroups, as
+// far as bits allow (whole words), and to 32 lanes each from 128 places on.
+// Whole operations, us: 147 chunks of 1 MiB unpacked 58.2 -> 51.5, 312 packed
+// 114.4 -> 106.9; a 190 MB state restored in 256 KiB chunks 120.4 -> 117.7, in
+// 128 KiB chunks 118.8 -> 117.4; up to 8 places nothing changes.  The bits' count costs
+// an atomic per workgroup with bits set, so the compare (4,000 flips: 206 ->
+// 207) and large states stay with 1,024 threads.
+constexpr uint32_t kFinalSmall = 16384;  // chunks
 
 template <int kMode>
 inline int launch_finalize_mode(const FinalArgs& f, uint32_t spc_shift, hipStream_t st) {
   if (f.n_chunks == 0) return 0;
   if (!f.parts || spc_shift == 0) return launch_finalize_as<kMode, 1, 2>(f, st);
   if (spc_shift < 4) return launch_finalize_as<kMode, 4, 2>(f, st);
+  constexpr int kThreads = kMode == kFold ? 256 : kMode == kCompare ? 512 : 1024;
+  if (spc_shift >= 7) return launch_finalize_as<kMode, 32, 8, kMode == kFold ? 256 : 1024>(f, st);
+  if (kMode == kFold || f.n_chunks <= kFinalSmall) {
+    if (spc_shift == 4) return launch_finalize_as<kMode, 16, 2, kThreads>(f, st);
+    return launch_finalize_as<kMode, 16, 4, kThreads>(f, st);
+  }
   if (spc_shift == 4) return launch_finalize_as<kMode, 16, 2>(f, st);
   return launch_finalize_as<kMode, 16, 4>(f, st);
 }
