@@ -306,7 +306,9 @@ int fr_verify_replicas(const fr_plan* plan, const void* base_a, const void* base
  *   sums_a, sums_b  device, 16-byte aligned, n_chunks entries each
  *   diff_bitmap     device, 4-byte aligned, bitmap_words words; written
  *   n_diff          device, 8-byte aligned, one uint64; zeroed by the call
- * Outputs must not overlap the inputs or each other (FR_E_OVERLAP). */
+ * Outputs must not overlap the inputs or each other (FR_E_OVERLAP).  Uses none
+ * of the plan's scratch: calls on several streams, and beside the plan's other
+ * operations, may overlap in time. */
 int fr_compare_sums(const fr_plan* plan, const fr_chunk_sum* sums_a, const fr_chunk_sum* sums_b,
                     uint32_t* diff_bitmap, uint64_t* n_diff, hipStream_t stream);
 

@@ -294,8 +294,7 @@ extern "C" int fr_compare_sums(const fr_plan* plan, const fr_chunk_sum* sums_a,
   const Region ins[] = {{sums_a, sb}, {sums_b, sb}};
   FR_TRY(check_disjoint(outs, 2, ins, 2));
   return launch_result(
-      launch_sums_compare(sums_a, sums_b, uint32_t(L.n_chunks), diff_bitmap, n_diff,
-                          plan->d_sums_arrive, stream));
+      launch_compare_sums(sums_a, sums_b, uint32_t(L.n_chunks), diff_bitmap, n_diff, stream));
 }
 
 extern "C" int fr_verify_replicas_noalloc(const fr_plan* plan, const void* base_a,

@@ -437,10 +437,10 @@ int launch_verify(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunk
                   const void* a, const void* b, uint32_t* bitmap, uint64_t* n_diff,
                   fr_chunk_sum* sums_a, fr_chunk_sum* sums_b, const Scratch& scr,
                   const LaunchCfg& cfg, void* stream);
-// Bit c of `bitmap` set iff the two sums of chunk c differ; `count` the bits set;
-// top: a word of the device that is zero between operations.
-FR_WEAK int launch_sums_compare(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
-                        uint32_t* bitmap, uint64_t* count, uint64_t* top, void* stream);
+// Bit c of `bitmap` set iff the two sums of chunk c differ; `count` the bits set.
+// Touches nothing but these buffers.
+int launch_compare_sums(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
+                        uint32_t* bitmap, uint64_t* count, void* stream);
 // The unit records of a delta list given as a bitmap, built on the device:
 // pack's SrcUnit list, or unpack's plain and derived lists, and the counts;
 // it also clears the accumulators of the listed positions and *zero_word,
@@ -524,7 +524,6 @@ struct fr_plan {
   // lines of arrivals and set bits, zero between operations, by which the last
   // workgroups of a kernel know that they are last (kernels.hip, Finish)
   uint64_t* d_arrive = nullptr;
-  uint64_t* d_sums_arrive = nullptr;  // the same for the compare of sums, which uses no other scratch
   uint32_t* h_delta_ids = nullptr;     // pinned staging of a host list
   hipEvent_t delta_ids_copied = nullptr;  // the last upload from the staging has completed
   fr::Scratch scratch{};

@@ -1368,8 +1368,6 @@ struct FinalArgs {
   const ChunkParts* parts;  // NULL: accumulators
   u64 part0, stride;        // of the slot walk the places belong to
   u64 tile_stride;          // of the tile walk
-  u64* top;  // NULL: the count has been cleared and is added to; else the plan's word of arrivals (zero
-             // between operations): the last workgroup to arrive has the count and stores it
 };
 
 // The sums of chunk c in `acc`, by the kLanes lanes of a group (`sub`: the
@@ -1479,15 +1477,7 @@ __global__ __launch_bounds__(kThreads) void k_finalize(FinalArgs f) {
     u64 t = 0;
 #pragma unroll
     for (int i = 0; i < kThreads / 64; i++) t += wave_count[i];
-    if (f.top) {
-      const u64 add = (t << 32) + 1, all = atomicAdd(f.top, add) + add;
-      if (uint32_t(all) == gridDim.x) {
-        *f.count = all >> 32;
-        __hip_atomic_store(f.top, u64(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    } else if (t) {
-      atomicAdd(f.count, t);
-    }
+    if (t) atomicAdd(f.count, t);
   }
 }
 
@@ -2477,18 +2467,18 @@ int launch_unpack_delta(const UnpackDeltaArgs& u, const LaunchCfg& cfg, void* st
   FR_DISPATCH(cfg.tile_unpack, unpack_delta_impl, u, cfg, hipStream_t(stream));
 }
 
-int launch_sums_compare(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
-                        uint32_t* bitmap, uint64_t* count, uint64_t* top, void* stream) {
+int launch_compare_sums(const fr_chunk_sum* a, const fr_chunk_sum* b, uint32_t n_chunks,
+                        uint32_t* bitmap, uint64_t* count, void* stream) {
   // the compare finalize with one accumulator per chunk: the first sums
-  // folded (as they are) against the second as the sums sent
+  // folded (as they are) against the second as the sums sent.  The count is
+  // cleared by a launch of its own: counting arrivals in a word of the plan
+  // saved it (3 us a call), but calls on several streams then shared that word
   const hipStream_t st = hipStream_t(stream);
-  if (n_chunks == 0) {
-    Zeroes z;
-    z.add(count, sizeof(u64));
-    return z.launch(st);
-  }
+  Zeroes z;
+  z.add(count, sizeof(u64));
+  const int e = z.launch(st);
+  if (e) return e;
   FinalArgs f{};
-  f.top = reinterpret_cast<u64*>(top);
   f.acc = a;
   f.sent = b;
   f.bitmap = bitmap;

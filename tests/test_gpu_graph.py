@@ -319,3 +319,41 @@ def test_two_plans_delta_calls_on_two_streams():
         assert torch.equal(b["payload"][:pb], r["payload"]) and torch.equal(b["sums"], r["sums"])
         assert torch.equal(b["dst"], r["dst"])
         assert torch.equal(b["bad"], r["bad"]) and torch.equal(b["nbad"], r["nbad"])
+
+
+def test_compare_sums_of_one_plan_on_several_streams():
+    """fr_compare_sums uses nothing of the plan but its sizes: calls of one
+    plan queued on four streams without ordering between them, beside whole
+    restores of the same plan on a fifth, each give their own bits and count
+    (and so does every later call)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    n = 40_000  # 40 workgroups of the finalize kernel
+    t = np.array([(0, 0, 4 * n, W.F32, -1)], dtype=W.TABLE_DTYPE)
+    plan = F.Plan(t, 16, 16 * n, 16 * n)
+    rng = np.random.default_rng(44)
+    src = torch.from_numpy(rng.integers(0, 256, size=16 * n, dtype=np.uint8)).to("cuda")
+    payload, sent, dst = plan.empty_payload(), plan.empty_sums(), torch.zeros_like(src)
+    bad, nbad, sums = plan.empty_bitmap(), plan.empty_counter(), plan.empty_sums()
+    plan.checksum_state(src, sums)
+    calls = []
+    for share in (0.0, 0.3, 1.0, 0.01):
+        want = np.flatnonzero(rng.random(n) < share)
+        other = sums.clone()
+        other[torch.from_numpy(want).to("cuda"), 1] ^= 4
+        calls.append((want, other, plan.empty_bitmap(), plan.empty_counter(), torch.cuda.Stream()))
+    restore = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for rep in range(20):
+        for want, other, bits, count, s in calls:
+            with torch.cuda.stream(s):
+                bits.fill_(-1)
+                count.fill_(-1)
+                plan.compare_sums(sums, other, bits, count, stream=s)
+        plan.pack(src, payload, sent, stream=restore)
+        plan.unpack(payload, sent, dst, bad, nbad, stream=restore)
+    torch.cuda.synchronize()
+    for want, _, bits, count, _ in calls:
+        assert int(count.item()) == want.size
+        assert np.array_equal(F.bitmap_indices(bits, n), want)
+    assert int(nbad.item()) == 0 and torch.equal(dst, src)
