@@ -66,10 +66,10 @@
  *   On any error nothing is enqueued and no output is touched.  A checksum or
  *   compare mismatch is data (a set bit and a count), not an error.
  *   Operations on one plan share the plan's device scratch: they must not run
- *   concurrently (issue them on one stream, or order the streams; the
- *   results of concurrent ones, and of later ones, are undefined), and one
+ *   concurrently (issue them on one stream, or order the streams), and one
  *   plan must not be used from several host threads at once; use one plan per
- *   concurrent stream.
+ *   concurrent stream.  (Of operations that do overlap the results are
+ *   undefined; later ones are not affected.)
  *   Graph capture.  The four whole-state operations, fr_compare_sums and
  *   the flagged delta calls enqueue kernel launches only (no memset, no
  *   host copy, no allocation), so a capture of them into a HIP graph

@@ -513,8 +513,10 @@ int unpack_list(const fr_plan* plan, const void* payload, uint64_t payload_bytes
   const uint64_t bound = list.bound;
   const bool whole = bound && plan->cfg.small & kSmallLists;
   if (bound) {
-    FR_TRY(launch_result(launch_delta_build(
-        delta_build(plan, list, nullptr, payload_bytes, plan->cfg.tile_unpack, n_bad), false, stream)));
+    DeltaBuild b = delta_build(plan, list, nullptr, payload_bytes, plan->cfg.tile_unpack, n_bad);
+    b.arrive = whole ? plan->d_list_arrive : nullptr;
+    b.arrive_n = bound;
+    FR_TRY(launch_result(launch_delta_build(b, false, stream)));
   }
   const uint64_t C = plan->layout.C;
   if (whole) {
@@ -527,6 +529,7 @@ int unpack_list(const fr_plan* plan, const void* payload, uint64_t payload_bytes
     m.sent = sums;
     m.bitmap = bad_bitmap;
     m.count = n_bad;
+    m.arrive = plan->d_list_arrive;
     m.list_counts = plan->d_delta_counts;
     m.exact = list.exact;
     m.bad = plan->scratch.flags;

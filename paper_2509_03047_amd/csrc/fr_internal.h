@@ -5,6 +5,7 @@
 
 #include <vector>
 
+#include "arrive.h"
 #include "flashrestore.h"
 
 namespace fr {
@@ -302,6 +303,8 @@ struct DeltaBuild {
   fr_chunk_sum* acc;         // accumulators of the operation, cleared per listed position, or NULL
   uint32_t acc_shift;        // log2 of the accumulators per list position
   uint64_t* zero_word;       // NULL, or a counter the operation starts from 0 (n_bad)
+  uint64_t* arrive;          // NULL, or the lines of arrivals of a list of at most arrive_n, cleared
+  uint64_t arrive_n;
 };
 
 // Bytes of one slice for a tile, and the accumulators a chunk of C bytes
@@ -360,13 +363,6 @@ struct UnpackBlocks {
 // An operation of a small state, one whole chunk per workgroup: the largest
 // chunk a workgroup of 1024 threads holds (four 16-byte vectors a thread).
 constexpr uint64_t kSmallChunk = uint64_t(1) << 16;
-constexpr uint64_t kArriveLine = 128, kArriveGroup = 64;
-// Bytes of the arrival lines for n chunks: one for all, one per bitmap word
-// and one per group of words.
-inline uint64_t arrive_bytes(uint64_t n) {
-  const uint64_t words = (n + 31) / 32;
-  return (1 + words + (words + kArriveGroup - 1) / kArriveGroup) * kArriveLine;
-}
 // Threads of a workgroup that holds a chunk of `longest` bytes.
 inline uint32_t small_threads(uint64_t longest) {
   uint32_t b = 64;
@@ -391,7 +387,7 @@ struct SmallArgs {
   fr_chunk_sum* sums = nullptr;  // compare: NULL or the first arena's
   fr_chunk_sum* sums_b = nullptr;
   uint32_t* flags = nullptr;   // one per chunk (scratch)
-  uint64_t* arrive = nullptr;  // the plan's d_arrive (lists: needed), or NULL: flags and a finalize launch
+  uint64_t* arrive = nullptr;  // the plan's d_arrive (lists: d_list_arrive), or NULL: flags and a finalize launch
   uint32_t* bitmap = nullptr;
   uint64_t* count = nullptr;
   // Lists built on the device.  n_chunks is the list's longest possible
@@ -521,9 +517,11 @@ struct fr_plan {
   uint32_t* d_delta_ids = nullptr;     // a host list, uploaded
   uint64_t* d_delta_payof = nullptr;   // per chunk: payload offset in the last delta unpack
   uint32_t* d_delta_m0 = nullptr;      // per chunk: a derived chunk's first master chunk
-  // lines of arrivals and set bits, zero between operations, by which the last
-  // workgroups of a kernel know that they are last (kernels.hip, Finish)
+  // lines of arrivals by which the last workgroups of a kernel know that they
+  // are last (arrive.h): the whole-state operations', zero between them, and
+  // the delta lists', which every list's builder clears
   uint64_t* d_arrive = nullptr;
+  uint64_t* d_list_arrive = nullptr;
   uint32_t* h_delta_ids = nullptr;     // pinned staging of a host list
   hipEvent_t delta_ids_copied = nullptr;  // the last upload from the staging has completed
   fr::Scratch scratch{};

@@ -1014,17 +1014,9 @@ __global__ __launch_bounds__(B) void k_pack_chunk(const SrcUnit* __restrict__ un
   }
 }
 
-// What becomes of the bits of an operation by whole chunks.  With `words`
-// (the plan's, zero between operations) the kernel writes the bitmap and the
-// count itself: a chunk adds its arrival (low half) and its bit (high half) to
-// its bitmap word's in one atomic, whoever brings the last arrival of a word
-// thereby holds all its bits, writes them, and adds the word's arrival and
-// count to its group's (of kArriveGroup words, where there are more) and then
-// to the first word the same way.  The data ride in the atomics, so nothing
-// has to be ordered or flushed between XCDs.  Every word has a line of its
-// own: atomics on one line follow each other at about 7 ns (16 words to a
-// line: 6,300 chunks of 4 KiB unpacked in 37 us instead of 31).  Without
-// `words` (the compare that allocates nothing, states of more than kArriveMost
+// What becomes of the bits of an operation by whole chunks.  With lines of
+// arrivals (arrive.h) the kernel writes the bitmap and the count itself.
+// Without (the compare that allocates nothing, states of more than kArriveMost
 // chunks) each chunk leaves a flag for the finalize kernel.
 // Against a finalize launch (us): 48 small tensors restored 21.5 -> 18.7, a
 // state of five 64 KiB chunks unpacked 12.5 -> 9.8, a repair of 20 chunks 42.1
@@ -1035,65 +1027,40 @@ __global__ __launch_bounds__(B) void k_pack_chunk(const SrcUnit* __restrict__ un
 // 64 KiB 215.6 -> 216.6, all of 11,800 578 -> 582).
 constexpr uint32_t kArriveMost = 8192;
 struct Finish {
-  u64* words;  // line 0: everything; lines 1 ...: bitmap words; behind them: groups of them
+  Arrivals arrive;  // lines NULL: flags
   uint32_t* flags;
-  uint32_t* bitmap;
-  u64* count;
-  u64 n;  // chunks the bitmap covers
 };
 
-__device__ __forceinline__ u64* arrive_line(const Finish& f, u64 i) {
-  return f.words + i * (kArriveLine / sizeof(u64));
-}
-__device__ __forceinline__ void arrive_reset(u64* line) {
-  __hip_atomic_store(line, u64(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// Lane 0's atomic.  The lane's index (0) in the address keeps it from being
+// uniform over the wave: the compiler would add up the wave's lanes first and
+// wait for each result at once, and taking a full word off its line would
+// stand between the word's arrival and its group's (51 MB compared with sums in
+// 24.1 us instead of 23.5).
+struct DeviceAtomic {
+  static __device__ __forceinline__ uint64_t add(uint64_t* line, uint64_t x) {
+    return atomicAdd(reinterpret_cast<u64*>(line + __lane_id()), u64(x));
+  }
+};
 
 // Workgroup's thread 0, once per chunk (those with on[k]) of the n chunks
-// there are: chunk c[k]'s bit.
-template <int N>
-__device__ __forceinline__ void finish_chunks(const Finish& f, u64 n, const u64 (&c)[N],
+// there are: chunk c[k]'s bit.  kKept: the lines are kept between calls, else
+// an earlier kernel of the call has cleared them.
+template <bool kKept, int N>
+__device__ __forceinline__ void finish_chunks(const Finish& f, u64 n, const uint64_t (&c)[N],
                                               const uint32_t (&bit)[N], const bool (&on)[N]) {
-  if (!f.words) {
-#pragma unroll
-    for (int k = 0; k < N; k++)
-      if (on[k]) f.flags[c[k]] = bit[k];
+  if (f.arrive.lines) {
+    arrive_chunks<DeviceAtomic, kKept>(f.arrive, n, c, bit, on);
     return;
   }
-  u64 now[N];
 #pragma unroll
-  for (int k = 0; k < N; k++) {  // all in flight together
-    if (!on[k]) continue;
-    const u64 add = (u64(bit[k]) << (32 + (c[k] & 31))) + 1;
-    now[k] = atomicAdd(arrive_line(f, 1 + (c[k] >> 5)), add) + add;
-  }
-#pragma unroll
-  for (int k = 0; k < N; k++) {
-    const u64 w = c[k] >> 5, here = n - 32 * w < 32 ? n - 32 * w : 32;
-    if (!on[k] || uint32_t(now[k]) != here) continue;
-    f.bitmap[w] = uint32_t(now[k] >> 32);
-    arrive_reset(arrive_line(f, 1 + w));
-    u64 bits = u64(__popcll(now[k] >> 32)), of = (n + 31) / 32;  // arrivals at the top
-    if (of > kArriveGroup) {
-      const u64 g = w / kArriveGroup, words = of - g * kArriveGroup < kArriveGroup ? of - g * kArriveGroup : kArriveGroup;
-      u64* line = arrive_line(f, 1 + (f.n + 31) / 32 + g);
-      const u64 add = (bits << 32) + 1, all = atomicAdd(line, add) + add;
-      if (uint32_t(all) != words) continue;
-      arrive_reset(line);
-      bits = all >> 32;
-      of = (of + kArriveGroup - 1) / kArriveGroup;
-    }
-    const u64 add = (bits << 32) + 1, all = atomicAdd(f.words, add) + add;
-    if (uint32_t(all) != of) continue;
-    *f.count = all >> 32;
-    arrive_reset(f.words);
-  }
+  for (int k = 0; k < N; k++)
+    if (on[k]) f.flags[c[k]] = bit[k];
 }
 
 // The end of a whole-state kernel whose bits go to the finalize kernel: the
 // count starts from 0 (last in the kernel, as in k_unpack).
 __device__ __forceinline__ void finish_end(const Finish& f) {
-  if (!f.words && blockIdx.x == 0 && threadIdx.x == 0) *f.count = 0;
+  if (!f.arrive.lines && blockIdx.x == 0 && threadIdx.x == 0) *f.arrive.count = 0;
 }
 
 // Whether each chunk differs; with kSums also both arenas' sums.
@@ -1140,7 +1107,7 @@ __global__ __launch_bounds__(B) void k_verify_chunk(const SrcUnit* __restrict__ 
         sums_a[r.c] = fr_chunk_sum{acc[0], acc[1]};
         sums_b[r.c] = fr_chunk_sum{acc[2], acc[3]};
       }
-      finish_chunks<1>(fin, n, {r.c}, {acc[K - 1] != 0}, {true});
+      finish_chunks<true, 1>(fin, n, {r.c}, {acc[K - 1] != 0}, {true});
     }
   }
   finish_end(fin);
@@ -1242,9 +1209,9 @@ __global__ __launch_bounds__(B) void k_unpack_chunk(const DerivedUnit* __restric
       block_sum<B, 6>(acc, lds, parity);
       parity ^= 1;
       if (threadIdx.x == 0)
-        finish_chunks<3>(fin, fin.n, {r.m0, r.m0 + u64(1), r.c},
-                         {differs(s0, acc[0], acc[1]), differs(s1, acc[2], acc[3]), differs(sp, acc[4], acc[5])},
-                         {true, two, true});
+        finish_chunks<true, 3>(fin, fin.arrive.n, {r.m0, r.m0 + u64(1), r.c},
+                               {differs(s0, acc[0], acc[1]), differs(s1, acc[2], acc[3]), differs(sp, acc[4], acc[5])},
+                               {true, two, true});
     } else {
       const PlainUnit r = plain[g - n_derived];
       const fr_chunk_sum s0 = sent[r.c];
@@ -1252,7 +1219,8 @@ __global__ __launch_bounds__(B) void k_unpack_chunk(const DerivedUnit* __restric
       unpack_plain_chunk<B>(r, payload, dst, acc);
       block_sum<B, 2>(acc, lds2, parity);
       parity ^= 1;
-      if (threadIdx.x == 0) finish_chunks<1>(fin, fin.n, {r.c}, {differs(s0, acc[0], acc[1])}, {true});
+      if (threadIdx.x == 0)
+        finish_chunks<true, 1>(fin, fin.arrive.n, {r.c}, {differs(s0, acc[0], acc[1])}, {true});
     }
   }
   finish_end(fin);
@@ -1325,11 +1293,11 @@ __global__ __launch_bounds__(B) void k_unpack_list_chunk(
     block_sum<B, 2>(acc, lds, parity);
     parity ^= 1;
     if (threadIdx.x == 0)
-      finish_chunks<1>(fin, n, {pos}, {differs(sent[pos], acc[0], acc[1]) | bad[pos]}, {true});
+      finish_chunks<false, 1>(fin, n, {pos}, {differs(sent[pos], acc[0], acc[1]) | bad[pos]}, {true});
   }
   // an empty list's count has been cleared by the list's builder
-  for (u64 w = (n + 31) / 32 + u64(blockIdx.x) * B + threadIdx.x; w < (fin.n + 31) / 32; w += u64(gridDim.x) * B)
-    fin.bitmap[w] = 0;  // past the list
+  for (u64 w = (n + 31) / 32 + u64(blockIdx.x) * B + threadIdx.x; w < (fin.arrive.n + 31) / 32; w += u64(gridDim.x) * B)
+    fin.arrive.bitmap[w] = 0;  // past the list
 }
 
 // -------------------------------------------------------------- finalize
@@ -1728,6 +1696,16 @@ __global__ __launch_bounds__(kListBlock) void k_list_build(DeltaBuild b, u64 n_b
   const DeltaAgg own = block_scan<kListBlock>(l.e, b.seg, excl);
   if (kPre != kPreScan && blockIdx.x + 1 == n_blocks && threadIdx.x == 0)
     list_totals(b, delta_then(before, own, b.seg));
+  if (!kForPack && b.arrive) {
+    // the lines of the list's bitmap words (at most 8 in a block's ids), of
+    // their groups and of everything
+    const u64 words = (b.arrive_n + 31) / 32, w = u64(blockIdx.x) * (kListBlock / 32) + threadIdx.x;
+    const u64 group = u64(blockIdx.x) * (kListBlock / 32) / kArriveGroup;
+    const Arrivals a{b.arrive, nullptr, nullptr, b.arrive_n};
+    if (threadIdx.x < kListBlock / 32 && w < words) *arrive_line(a, 1 + w) = 0;
+    if (threadIdx.x == 64 && group * kArriveGroup < words) *group_line(a, group) = 0;
+    if (threadIdx.x == 128 && blockIdx.x == 0) *arrive_line(a, 0) = 0;
+  }
   if (!l.on) return;
   const u64 A = b.seg;
   const uint32_t pos = pre.ns + pre.nd + excl.ns + excl.nd;  // list position
@@ -2266,7 +2244,7 @@ int small_impl(const SmallArgs& m, hipStream_t st) {
   }
   u64* count = reinterpret_cast<u64*>(m.count);
   const bool arrive = m.arrive && (m.list_counts || m.n_chunks <= kArriveMost);
-  const Finish fin{arrive ? reinterpret_cast<u64*>(m.arrive) : nullptr, m.flags, m.bitmap, count, m.n_chunks};
+  const Finish fin{Arrivals{arrive ? m.arrive : nullptr, m.bitmap, m.count, m.n_chunks}, m.flags};
   if (m.op == SmallArgs::kUnpack) {
     const dim3 grid(grid_for<B>(u64(m.n_derived) + m.n_plain, m.cfg));
     hipLaunchKernelGGL((k_unpack_chunk<B>), grid, block, 0, st, m.derived, u64(m.n_derived), m.plain,

@@ -848,9 +848,9 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
   const uint64_t b_agg = up(nb * sizeof(DeltaAgg)), b_pre = up(nb * sizeof(DeltaPre));
   const uint64_t b_counts = 256, b_bits = up(nw * 4), b_ids = up(nc * 4), b_payof = up(nc * 8);
   const uint64_t b_parts = (p->cfg.small & kSmallAll) == kSmallAll ? 0 : up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
-  const uint64_t b_arrive = up(arrive_bytes(nc));
+  const uint64_t b_arrive = up(arrive_bytes(nc));  // twice: zeros, and the lists'
   const uint64_t total =
-      b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids + b_arrive + b_parts;
+      b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids + 2 * b_arrive + b_parts;
   int rc = upload(nullptr, total, &p->d_delta, st.s);
   if (rc != FR_OK) return rc;
   uint8_t* q = static_cast<uint8_t*>(p->d_delta);
@@ -874,6 +874,7 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
   p->d_delta_payof = reinterpret_cast<uint64_t*>(take(b_payof));
   p->d_delta_m0 = reinterpret_cast<uint32_t*>(take(b_ids));
   p->d_arrive = reinterpret_cast<uint64_t*>(take(b_arrive));
+  p->d_list_arrive = reinterpret_cast<uint64_t*>(take(b_arrive));
   st.parts = reinterpret_cast<ChunkParts*>(take(b_parts));
   std::vector<ChunkLoc> loc(nc);
   std::vector<uint32_t> m0((b_ids + b_arrive) / 4, 0);  // and d_arrive's zeros behind them

@@ -71,3 +71,35 @@ def test_bits_and_counts_over_calls_in_a_row(n, monkeypatch):
         check(wrong, f"list {share}")
         if p == 0 or share in (0.0, 1.0):
             assert torch.equal(other, src)
+
+
+def test_calls_after_overlapping_ones_are_right(monkeypatch):
+    """Whole-state calls of one plan on two streams without ordering (against
+    the rule: their own bits and counts are undefined, their bytes are not)
+    leave nothing behind for the calls after them."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    monkeypatch.setenv("FLASHRESTORE_SMALL", str(1 << 30))
+    n = 4097
+    t = np.array([(0, 0, n * C // 4, W.F32, -1)], dtype=W.TABLE_DTYPE)
+    plan = F.Plan(t, C, n * C, n * C)
+    rng = np.random.default_rng(9)
+    src = torch.from_numpy(rng.integers(0, 256, size=n * C, dtype=np.uint8)).cuda()
+    payload, sums, dst = plan.empty_payload(), plan.empty_sums(), torch.zeros_like(src)
+    plan.pack(src, payload, sums)
+    other = src.clone()
+    want = np.flatnonzero(rng.random(n) < 0.2)
+    other[torch.from_numpy(want * C).cuda()] ^= 1
+    mine = [(plan.empty_bitmap(), plan.empty_counter(), torch.cuda.Stream()) for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(50):
+        (b0, c0, s0), (b1, c1, s1) = mine
+        plan.verify_replicas(src, other, b0, c0, stream=s0)
+        plan.unpack(payload, sums, dst, b1, c1, stream=s1)
+    torch.cuda.synchronize()
+    assert torch.equal(dst, src)
+    for bits, count, _ in mine:
+        plan.verify_replicas(src, other, bits.fill_(-1), count.fill_(-1))
+        assert int(count.item()) == want.size and np.array_equal(F.bitmap_indices(bits, n), want)
+        plan.unpack(payload, sums, dst, bits.fill_(-1), count.fill_(-1))
+        assert int(count.item()) == 0 and F.bitmap_indices(bits, n).size == 0
