@@ -36,15 +36,18 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, 8 TB/s
 METRIC = "state restore GB/s per GPU (pack+checksum, unpack+verify) and % of HBM peak"
-KERNEL_SOURCES = ("paper_2509_03047_amd/csrc/kernels.hip", "paper_2509_03047_amd/csrc/fr_internal.h")
+KERNEL_SOURCES = ("paper_2509_03047_amd/csrc/kernels.hip", "paper_2509_03047_amd/csrc/fr_internal.h",
+                  "paper_2509_03047_amd/csrc/arrive.h")
 # HBM traffic per launch measured with rocprofv3 counters, per workload
 TRAFFIC_FILES = {1: "hbm_traffic_llama8b_tp8.json", 2: "hbm_traffic_descriptor_stress_20k.json",
                  3: "hbm_traffic_llama70b_tp8pp4.json"}
 KERNEL_NAMES = {"pack": "k_pack", "unpack": "k_unpack", "verify": "k_verify", "checksum": "k_pack"}
-WALK_TILES = 4  # fr_plan_info pack_walk / unpack_walk: one aligned tile of the side written per workgroup
-TILE_KERNELS = {"pack": "k_pack_blocks", "unpack": "k_unpack_blocks"}
+# fr_plan_info pack_walk / unpack_walk: one aligned tile of the side written, or one whole chunk, per workgroup
+WALK_TILES, WALK_CHUNKS = 4, 5
+WALK_KERNELS = {WALK_TILES: {"pack": "k_pack_blocks", "unpack": "k_unpack_blocks"},
+                WALK_CHUNKS: {"pack": "k_pack_chunk", "unpack": "k_unpack_chunk"}}
 WALK_NAMES = {0: "slices", 1: "slices cut at arena / receiver lines", 2: "slices cut at payload lines",
-              3: "slices cut at payload slice boundaries", WALK_TILES: "tiles of the side written"}
+              3: "slices cut at payload slice boundaries", WALK_TILES: "tiles of the side written", WALK_CHUNKS: "whole chunks"}
 # fr_plan_info tile_*: threads x 16-byte vectors per workgroup
 TILE_SHAPES = ("256x1", "512x1", "256x2", "256x4", "64x4", "128x2", "64x2", "64x1", "128x1", "128x4", "64x8")
 
@@ -662,7 +665,7 @@ def main():
                          "hbm_gbs": round(gbs, 1), "frac_of_peak": round(gbs / HBM_PEAK_GBS, 4)}
     dom = max(ops, key=lambda o: per_op[o])
     walks = {"pack": info["pack_walk"], "unpack": info["unpack_walk"]}
-    kernel = TILE_KERNELS[dom] if walks.get(dom) == WALK_TILES else KERNEL_NAMES[dom]
+    kernel = WALK_KERNELS.get(walks.get(dom), KERNEL_NAMES)[dom]
     roof = {"bound": "hbm", "kernel": kernel, "op": dom,
             "achieved": op_report[dom]["hbm_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": op_report[dom]["frac_of_peak"], "traffic": None}

@@ -152,18 +152,20 @@ typedef struct fr_plan_info {
                                aligned tile of the side written (the payload for
                                pack, the receiver arena for unpack) per workgroup,
                                the default where that side's chunks start inside
-                               cache lines; FR_WALK_*.  (Of states too large to
-                               take whole chunks, see fr_plan_create) */
-  uint32_t tile_pack;       /* the tile each operation launches with, 0-10 (threads x */
+                               cache lines, 5 one whole chunk per workgroup (small
+                               states, see fr_plan_create); FR_WALK_* */
+  uint32_t tile_pack;       /* the tile of each operation's walk, 0-10 (threads x */
   uint32_t tile_unpack;     /* 16-byte vectors per workgroup: 256x1, 512x1, 256x2, */
   uint32_t tile_verify;     /* 256x4, 64x4, 128x2, 64x2, 64x1, 128x1, 128x4, 64x8): */
-  uint32_t tile_checksum;   /* set by FLASHRESTORE_TILE*, else chosen by chunk size;
-                               a layout query reports what a plan created now, in
-                               the same environment, would take */
+  uint32_t tile_checksum;   /* set by FLASHRESTORE_TILE*, else chosen by chunk size
+                               (an operation that takes whole chunks uses none); a
+                               layout query reports what a plan created now, in the
+                               same environment, would have */
 } fr_plan_info;
 
 #define FR_WALK_SLICES 0
 #define FR_WALK_TILES 4
+#define FR_WALK_CHUNKS 5
 
 /* ---------------------------------------------------------------- plans */
 

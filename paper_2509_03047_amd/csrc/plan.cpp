@@ -998,10 +998,12 @@ extern "C" int fr_plan_get_info(const fr_plan* p, fr_plan_info* info) {
   // the walks the operations take (a line-aligned mode is the plain walk
   // where every chunk of its side starts on a line)
   const LaunchCfg& c = p->cfg;
-  const uint32_t pw = c.line_pack == kLineBlocks ? uint32_t(kLineBlocks)
-                                                 : line_walk(p, c.tile_pack, c.line_pack);
-  const uint32_t uw = c.line_unpack == kLineBlocks ? uint32_t(kLineBlocks)
-                                                   : line_walk(p, c.tile_unpack, c.line_unpack, true);
+  const uint32_t pw = c.small & kSmallPack         ? uint32_t(FR_WALK_CHUNKS)
+                      : c.line_pack == kLineBlocks ? uint32_t(kLineBlocks)
+                                                   : line_walk(p, c.tile_pack, c.line_pack);
+  const uint32_t uw = c.small & kSmallUnpack         ? uint32_t(FR_WALK_CHUNKS)
+                      : c.line_unpack == kLineBlocks ? uint32_t(kLineBlocks)
+                                                     : line_walk(p, c.tile_unpack, c.line_unpack, true);
   fill_info(p->layout, uint32_t(p->table.size()), p->src_arena_bytes, p->dst_arena_bytes,
             p->device, c, info, pw, uw);
   return FR_OK;

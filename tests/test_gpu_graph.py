@@ -25,8 +25,18 @@ def _scattered_case(C=4096):
     return t, C, sb, sb, W.random_tiny_state(t, sb, rng)
 
 
+def _small(monkeypatch, small):
+    """FLASHRESTORE_SMALL unset: small states take whole chunks; 0: walks and
+    their folds, as large states do."""
+    if small is None:
+        monkeypatch.delenv("FLASHRESTORE_SMALL", raising=False)
+    else:
+        monkeypatch.setenv("FLASHRESTORE_SMALL", small)
+
+
+@pytest.mark.parametrize("small", [None, "0"])  # as small states run by default, and as large ones do
 @pytest.mark.parametrize("case", ["toy", "scattered", "scattered 1 KiB chunks"])
-def test_captured_restore_step_replays_correctly(case, monkeypatch):
+def test_captured_restore_step_replays_correctly(case, small, monkeypatch):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     if case == "toy":
@@ -36,9 +46,15 @@ def test_captured_restore_step_replays_correctly(case, monkeypatch):
         table, C, sb, db, src_np = _scattered_case(1024 if "1 KiB" in case else 4096)
     for k in [k for k in os.environ if k.startswith("FLASHRESTORE_TILE")]:
         monkeypatch.delenv(k)
+    _small(monkeypatch, small)
     plan = F.Plan(table, C, sb, db)
-    if case != "toy":
-        assert plan.info["pack_walk"] == 4 and plan.info["unpack_walk"] == 4
+    walks = (plan.info["pack_walk"], plan.info["unpack_walk"])
+    if small is None:  # (unpack takes no whole chunks of 1 KiB)
+        assert walks == ((5, 4) if "1 KiB" in case else (5, 5))
+    elif case != "toy":
+        assert walks == (4, 4)
+    else:
+        assert 5 not in walks
     if "1 KiB" in case:
         assert (plan.info["tile_unpack"], plan.info["tile_verify"], plan.info["tile_checksum"]) == (7, 7, 4)
     src = torch.from_numpy(src_np).to("cuda")
@@ -108,13 +124,15 @@ def test_captured_restore_step_replays_correctly(case, monkeypatch):
     assert torch.equal(dst[covered], ref[2][covered]) and torch.equal(csum, ref[3])
 
 
-def test_captured_compare_and_repair_replays_correctly():
+@pytest.mark.parametrize("small", [None, "0"])
+def test_captured_compare_and_repair_replays_correctly(small, monkeypatch):
     """Replica compare -> delta pack of the flagged chunks -> delta unpack
     into the replica, captured once and replayed on a different divergence
     each time: the replica equals the donor again, and the delta payload and
     sums equal the oracle's for the flagged list."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    _small(monkeypatch, small)
     from oracle import cpu
 
     w = W.make_workload(0)
@@ -164,7 +182,8 @@ def test_captured_compare_and_repair_replays_correctly():
         assert int(nbad.item()) == 0 and torch.equal(replica, donor), rep
 
 
-def test_captured_sums_check_and_repair_replays_correctly():
+@pytest.mark.parametrize("small", [None, "0"])
+def test_captured_sums_check_and_repair_replays_correctly(small, monkeypatch):
     """The cross-GPU form of the same repair, on one GPU: checksum of each
     replica -> fr_compare_sums of the two sums arrays -> delta pack of the
     flagged chunks -> delta unpack, captured once and replayed on a
@@ -172,6 +191,7 @@ def test_captured_sums_check_and_repair_replays_correctly():
     of the two replicas' sums, and the replica equals the donor again."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    _small(monkeypatch, small)
     from oracle import cpu
 
     w = W.make_workload(0)
@@ -222,12 +242,14 @@ def test_captured_sums_check_and_repair_replays_correctly():
         assert int(nbad.item()) == 0 and torch.equal(replica, donor), rep
 
 
-def test_two_plans_on_two_streams_run_concurrently():
+@pytest.mark.parametrize("small", [None, "0"])
+def test_two_plans_on_two_streams_run_concurrently(small, monkeypatch):
     """One plan per concurrent stream: two plans' whole restore steps, queued
     on two streams without ordering between them, give the same results as
     each plan run alone."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    _small(monkeypatch, small)
     rng = np.random.default_rng(5)
     runs = []
     for seed in (0, 1):
@@ -271,12 +293,14 @@ def test_two_plans_on_two_streams_run_concurrently():
         assert int(b["nbad"].item()) == 0
 
 
-def test_two_plans_delta_calls_on_two_streams():
+@pytest.mark.parametrize("small", [None, "0"])
+def test_two_plans_delta_calls_on_two_streams(small, monkeypatch):
     """Delta calls of two plans (each with its own unit-record buffer) queued
     on two streams without ordering between them give each plan's serial
     results."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    _small(monkeypatch, small)
     rng = np.random.default_rng(6)
     runs = []
     for _ in range(2):

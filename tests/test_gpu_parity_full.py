@@ -110,9 +110,10 @@ def test_llama8b_tp8_full_parity(llama8b):
 @pytest.mark.timeout(900)
 def test_llama8b_1kib_chunks_full_parity(llama8b, monkeypatch):
     """The 8B share in 1 KiB chunks (13.7 million chunks) with the tiles chosen
-    by chunk size (unpack and compare 64 x 1, checksum 64 x 4): whole
-    oracle for pack, unpack, compare and checksum."""
-    for k in [k for k in os.environ if k.startswith("FLASHRESTORE_TILE")]:
+    by chunk size (unpack and compare 64 x 1; checksum whole chunks, and its
+    64 x 4 tiles where whole chunks are switched off): whole oracle for pack,
+    unpack, compare and checksum."""
+    for k in [k for k in os.environ if k.startswith(("FLASHRESTORE_TILE", "FLASHRESTORE_SMALL"))]:
         monkeypatch.delenv(k)
     w, src_np = llama8b
     t, C = w.table, 1024
@@ -137,6 +138,11 @@ def test_llama8b_1kib_chunks_full_parity(llama8b, monkeypatch):
     assert nbad == 0 and int(r.n_bad.item()) == 0 and r.bad_set() == set()
     assert np.array_equal(to_host(r.dst), dst)
     assert int(r.n_diff.item()) == 0 and r.diff_set() == set()
+    assert np.array_equal(sums_host(r.csum, nc), sums)
+    monkeypatch.setenv("FLASHRESTORE_SMALL", "0")
+    walks = F.Plan(t, C, w.src_arena_bytes, w.dst_arena_bytes)
+    r.csum.fill_(-1)
+    walks.checksum_state(r.dst, r.csum)
     assert np.array_equal(sums_host(r.csum, nc), sums)
 
 

@@ -565,10 +565,12 @@ def test_walks_follow_the_alignment_of_the_side_written():
     """By default pack walks tiles of the payload where payload chunks start
     inside cache lines and unpack tiles of the receiver where receiver chunks
     do; otherwise both walk slices (plan info reports the walk taken), and
-    either way the restore equals the oracle's."""
+    either way the restore equals the oracle's.  A state this small takes
+    whole chunks by default, pack from 1 KiB chunks on and unpack from 2 KiB;
+    FLASHRESTORE_SMALL=0 leaves the walks."""
     from paper_2509_03047_amd import flashrestore as F
 
-    names = ("FLASHRESTORE_LINE", "FLASHRESTORE_LINE_PACK", "FLASHRESTORE_LINE_UNPACK")
+    names = ("FLASHRESTORE_LINE", "FLASHRESTORE_LINE_PACK", "FLASHRESTORE_LINE_UNPACK", "FLASHRESTORE_SMALL")
     old = {k: os.environ.pop(k, None) for k in names}
     rng = np.random.default_rng(77)
     try:
@@ -586,6 +588,11 @@ def test_walks_follow_the_alignment_of_the_side_written():
             t = table.copy()
             t["src_offset"], t["dst_offset"] = so, do
             sb, db = so[-1] + 1344, do[-1] + 1344
+            os.environ.pop("FLASHRESTORE_SMALL", None)
+            for C, walks in ((512, (5, want[1])), (1024, (5, want[1])), (2048, (5, 5)), (65536, (5, 5))):
+                plan = F.Plan(t, C, sb, db, segment_align=seg)
+                assert (plan.info["pack_walk"], plan.info["unpack_walk"]) == walks, (C, so, do, seg)
+            os.environ["FLASHRESTORE_SMALL"] = "0"
             plan = F.Plan(t, 1024, sb, db, segment_align=seg)
             assert (plan.info["pack_walk"], plan.info["unpack_walk"]) == want, (so, do, seg)
             # the tiles the plan took are the ones a layout query predicts
@@ -596,6 +603,7 @@ def test_walks_follow_the_alignment_of_the_side_written():
             src = W.random_tiny_state(t, sb, rng)
             _check_against_oracle(t, 1024, src, sb, db, corrupt_rng=rng, seg=seg, tag=f"walks {want}")
     finally:
+        os.environ.pop("FLASHRESTORE_SMALL", None)
         for k, v in old.items():
             if v is not None:
                 os.environ[k] = v
