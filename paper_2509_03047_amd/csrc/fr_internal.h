@@ -404,11 +404,8 @@ struct SmallArgs {
 };
 
 // Kernel launchers (kernels.hip).  They assume validated arguments, enqueue
-// on `stream` and return the hipError_t of the launches as an int.  (Those
-// marked weak: host-only builds of the plan code and the entry points, which
-// have no kernels and create no plan, link without them.)
-#define FR_WEAK __attribute__((weak))
-FR_WEAK int launch_small(const SmallArgs& args, void* stream);
+// on `stream` and return the hipError_t of the launches as an int.
+int launch_small(const SmallArgs& args, void* stream);
 // `units` holds n_chunks records whose sums slots c cover [0, n_chunks);
 // `slots` walks them at the slice size of the operation's tile.
 int launch_pack(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunks, uint64_t C,
@@ -457,13 +454,13 @@ int launch_expand_slots(const uint64_t* first, const uint64_t* base, uint64_t n_
 // out[chunk] <- its slots, from the same runs: a unit is the chunk of its own
 // index (derived and plain NULL), or an unpack unit, whose derived groups of
 // 2^spc_shift slots per master chunk cover three chunks.
-FR_WEAK int launch_slot_parts(const uint64_t* first, const uint64_t* base, uint64_t n_runs,
+int launch_slot_parts(const uint64_t* first, const uint64_t* base, uint64_t n_runs,
                       const DerivedUnit* derived, const PlainUnit* plain, uint32_t spc_shift,
                       ChunkParts* out, void* stream);
 // out[chunk] <- its places in a walk of payload tiles (pack) or of receiver
 // tiles (unpack; each unit's dlead holds the rank of its first tile).
-FR_WEAK int launch_pack_tile_parts(const PackBlocks& pb, uint32_t tile_vecs, ChunkParts* out, void* stream);
-FR_WEAK int launch_unpack_tile_parts(const UnpackBlocks& ub, uint32_t tile_vecs, ChunkParts* out, void* stream);
+int launch_pack_tile_parts(const PackBlocks& pb, uint32_t tile_vecs, ChunkParts* out, void* stream);
+int launch_unpack_tile_parts(const UnpackBlocks& ub, uint32_t tile_vecs, ChunkParts* out, void* stream);
 
 }  // namespace fr
 

@@ -45,6 +45,11 @@ int launch_verify(const SrcUnit*, const SlotTable&, uint32_t, uint64_t, const vo
                   const LaunchCfg&, void*) { return 1; }
 int launch_expand_slots(const uint64_t*, const uint64_t*, uint64_t, uint64_t, uint64_t, uint64_t*,
                         void*) { return 1; }
+int launch_small(const SmallArgs&, void*) { return 1; }
+int launch_slot_parts(const uint64_t*, const uint64_t*, uint64_t, const DerivedUnit*, const PlainUnit*,
+                      uint32_t, ChunkParts*, void*) { return 1; }
+int launch_pack_tile_parts(const PackBlocks&, uint32_t, ChunkParts*, void*) { return 1; }
+int launch_unpack_tile_parts(const UnpackBlocks&, uint32_t, ChunkParts*, void*) { return 1; }
 }  // namespace fr
 
 namespace {

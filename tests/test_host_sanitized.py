@@ -34,3 +34,21 @@ def test_host_code_under_sanitizers(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=600, env=env)
     assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
     assert "0 delta layout mismatches" in r.stdout
+
+
+def test_host_code_needs_every_launcher(tmp_path):
+    """The host sources refer to the kernel launchers strongly: a library built
+    without one of them must not link (a weak one would be a call to NULL)."""
+    if shutil.which("g++") is None or not os.path.isdir(os.path.join(ROCM, "include", "hip")):
+        pytest.skip("needs g++ and the HIP headers")
+    refs = {}
+    for f in ("plan.cpp", "api.cpp"):
+        o = str(tmp_path / (f + ".o"))
+        subprocess.run(["g++", "-std=c++17", "-O1", "-c", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"),
+                        "-I", os.path.join(ROCM, "include"), os.path.join(CSRC, f), "-o", o], check=True, timeout=300)
+        for line in subprocess.run(["nm", "-C", "-u", o], check=True, capture_output=True, text=True).stdout.splitlines():
+            kind, name = line.strip().split(" ", 1)
+            if name.startswith("fr::launch_"):
+                refs[name.split("(")[0]] = kind
+    assert "fr::launch_small" in refs and "fr::launch_slot_parts" in refs
+    assert set(refs.values()) == {"U"}, refs
