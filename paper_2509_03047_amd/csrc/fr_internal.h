@@ -501,6 +501,7 @@ struct fr_plan {
   uint32_t n_plain = 0;
   void* d_scratch = nullptr;         // one allocation holding `scratch`
   uint64_t n_places = 0;             // partial sums the longest walk stores
+  uint64_t n_places_b = 0;           // the same of the walks that store two sets
   // Delta lists, built on the device (one allocation, carved at creation):
   void* d_delta = nullptr;
   fr::ChunkLoc* d_delta_loc = nullptr;  // per chunk id

@@ -567,9 +567,10 @@ void take_parts(fr_plan::Walk& w, const Layout& L, Staging& st) {
 }
 
 // The plan's partial sums must hold a walk's places: `tiles` of a tile walk,
-// then one per entry of the slot table.
-void need_places(fr_plan* p, const SlotTable& t, uint64_t tiles) {
+// then one per entry of the slot table; with `two`, in both sets.
+void need_places(fr_plan* p, const SlotTable& t, uint64_t tiles, bool two) {
   p->n_places = std::max(p->n_places, tiles + 8 * t.stride);
+  if (two) p->n_places_b = std::max(p->n_places_b, tiles + 8 * t.stride);
 }
 
 // Walks of pack / checksum / compare: every chunk once, one table per slice
@@ -602,9 +603,13 @@ int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st) 
     const uint32_t shift = line_walk(p, tw.tile, tw.line);
     const uint32_t absorb = shift && tw.absorb ? 1u : 0u;
     const bool arena = tw.arena && !p->chunks_in_arena_order;
+    const bool compare = &tw == &walks[2], sums = !compare || !(p->cfg.small & kSmallVerifySums);
     bool have = false;
-    for (const auto& w : p->src_walks)
-      have = have || (w.sl == sl && w.t.shift == shift && w.t.absorb == absorb && w.arena_order == arena);
+    for (const auto& w : p->src_walks) {
+      if (w.sl != sl || w.t.shift != shift || w.t.absorb != absorb || w.arena_order != arena) continue;
+      have = true;
+      if (w.parts && compare && sums) need_places(p, w.t, 0, true);
+    }
     if (have) continue;
     if (arena && by_addr.empty()) {  // entries by sender offset, each entry's chunks in order
       std::vector<uint32_t> ent(p->table.size());
@@ -630,11 +635,11 @@ int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st) 
     w.t.absorb = absorb;
     w.arena_order = arena;
     // with one slot per chunk a slice's sums are the chunk's: a small state
-    // needs no partial sums
-    if (b.n() != L.n_chunks || L.n_chunks > kWholeChunks) take_parts(w, L, st);
+    // needs no partial sums; nor does a walk that only compares bytes
+    if (sums && (b.n() != L.n_chunks || L.n_chunks > kWholeChunks)) take_parts(w, L, st);
     const int rc = upload_walk(b, w, st, w.parts);
     if (rc != FR_OK) return rc;
-    need_places(p, w.t, 0);
+    if (w.parts) need_places(p, w.t, 0, compare);
   }
   return FR_OK;
 }
@@ -681,7 +686,7 @@ int build_pack_blocks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st
     if (e != hipSuccess) rc = hip_fail(e);
   }
   p->pack_extra.t.part0 = 16 * pb.stride + pb.n_units;  // behind the tiles' (tile_place)
-  need_places(p, p->pack_extra.t, p->pack_extra.t.part0);
+  need_places(p, p->pack_extra.t, p->pack_extra.t.part0, false);
   pb.extra = p->pack_extra.t;
   return rc;
 }
@@ -767,7 +772,7 @@ int build_unpack_blocks(fr_plan* p, const std::vector<ChunkRec>& recs,
     if (e != hipSuccess) rc = hip_fail(e);
   }
   p->unpack_derived.t.part0 = 16 * ub.stride + ub.n_units;
-  need_places(p, p->unpack_derived.t, p->unpack_derived.t.part0);
+  need_places(p, p->unpack_derived.t, p->unpack_derived.t.part0, p->n_derived != 0);
   ub.derived = p->unpack_derived.t;
   return rc;
 }
@@ -804,28 +809,31 @@ int build_unpack_walk(fr_plan* p, const std::vector<ChunkRec>& recs,
   const int rc = upload_walk(b, p->unpack_walk, st, p->unpack_walk.parts, p);
   p->unpack_walk.t.shift = line;
   p->unpack_walk.t.absorb = absorb;
-  need_places(p, p->unpack_walk.t, 0);
+  need_places(p, p->unpack_walk.t, 0, p->n_derived != 0);
   return rc;
 }
 
 // Scratch: two sets of partial sums, one place per slot of the longest walk
-// (16 bytes per 4 KiB slice: 0.4 % of the state each), which also hold the
-// delta calls' accumulators (the largest G their tiles need per chunk), and
-// one flag per chunk.
+// (16 bytes per 4 KiB slice: 0.4 % of the state each), the second only as long
+// as the walks that keep two sums a slot need it (the compare with sums, and
+// unpack's derived groups); the first also holds the accumulators of the delta
+// calls that take slices (the largest G their tiles need per chunk).  And one
+// flag per chunk.
 int build_scratch(fr_plan* p, const Staging& st) {
   const Layout& L = p->layout;
-  uint64_t g = 1;
-  for (int t : {p->cfg.tile_pack, p->cfg.tile_unpack})
-    g = std::max<uint64_t>(g, accumulators_per_chunk(L.C, t));
-  const uint64_t acc_bytes =
-      (std::max(L.n_chunks * g, p->n_places) * sizeof(fr_chunk_sum) + 255) & ~uint64_t(255);
+  uint64_t g = 0;
+  if (!(p->cfg.small & kSmallLists))
+    for (int t : {p->cfg.tile_pack, p->cfg.tile_unpack})
+      g = std::max<uint64_t>(g, accumulators_per_chunk(L.C, t));
+  auto bytes = [](uint64_t places) { return (places * sizeof(fr_chunk_sum) + 255) & ~uint64_t(255); };
+  const uint64_t acc_bytes = bytes(std::max(L.n_chunks * g, p->n_places)), acc_b_bytes = bytes(p->n_places_b);
   const uint64_t flag_bytes = (L.n_chunks * 4 + 255) & ~uint64_t(255);
-  const int rc = upload(nullptr, 2 * acc_bytes + flag_bytes, &p->d_scratch, st.s);
+  const int rc = upload(nullptr, acc_bytes + acc_b_bytes + flag_bytes, &p->d_scratch, st.s);
   if (rc == FR_OK && p->d_scratch) {
     uint8_t* base = static_cast<uint8_t*>(p->d_scratch);
     p->scratch.acc = reinterpret_cast<fr_chunk_sum*>(base);
     p->scratch.acc_b = reinterpret_cast<fr_chunk_sum*>(base + acc_bytes);
-    p->scratch.flags = reinterpret_cast<uint32_t*>(base + 2 * acc_bytes);
+    p->scratch.flags = reinterpret_cast<uint32_t*>(base + acc_bytes + acc_b_bytes);
   }
   return rc;
 }
@@ -847,7 +855,9 @@ int build_delta(fr_plan* p, const std::vector<ChunkRec>& recs, Staging& st) {
                                                               (nc - L.n_sent_chunks) * sizeof(DerivedUnit)));
   const uint64_t b_agg = up(nb * sizeof(DeltaAgg)), b_pre = up(nb * sizeof(DeltaPre));
   const uint64_t b_counts = 256, b_bits = up(nw * 4), b_ids = up(nc * 4), b_payof = up(nc * 8);
-  const uint64_t b_parts = (p->cfg.small & kSmallAll) == kSmallAll ? 0 : up(4 * nc * sizeof(ChunkParts));  // pack, checksum, compare, unpack
+  uint64_t walks = 0;  // that keep partial sums
+  for (uint32_t op : {kSmallPack, kSmallUnpack, kSmallVerifySums, kSmallChecksum}) walks += !(p->cfg.small & op);
+  const uint64_t b_parts = up(walks * nc * sizeof(ChunkParts));
   const uint64_t b_arrive = up(arrive_bytes(nc));  // twice: zeros, and the lists'
   const uint64_t total =
       b_loc + b_units + b_agg + b_pre + b_counts + b_bits + b_ids + b_payof + b_ids + 2 * b_arrive + b_parts;
