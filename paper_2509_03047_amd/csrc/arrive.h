@@ -34,7 +34,7 @@ namespace fr {
 // Every line has 128 bytes of its own: atomics on one line follow each other at
 // about 7 ns (16 words to a line: 6,300 chunks of 4 KiB unpacked in 37 us
 // instead of 31).
-constexpr uint64_t kArriveLine = 128, kArriveGroup = 64;
+constexpr uint32_t kArriveLine = 128, kArriveGroup = 64;
 // Bytes of the lines for n chunks: one for all, one per bitmap word and one per
 // group of words.
 inline uint64_t arrive_bytes(uint64_t n) {
@@ -49,11 +49,11 @@ struct Arrivals {
   uint64_t n;        // chunks the lines are laid out for
 };
 
-FR_DEVICE uint64_t* arrive_line(const Arrivals& a, uint64_t i) {
-  return a.lines + i * (kArriveLine / sizeof(uint64_t));
+FR_DEVICE uint64_t* arrive_line(const Arrivals& a, uint32_t i) {
+  return a.lines + uint64_t(i) * (kArriveLine / sizeof(uint64_t));
 }
-FR_DEVICE uint64_t* group_line(const Arrivals& a, uint64_t g) {
-  return arrive_line(a, 1 + (a.n + 31) / 32 + g);
+FR_DEVICE uint64_t* group_line(const Arrivals& a, uint32_t g) {
+  return arrive_line(a, 1 + uint32_t((a.n + 31) / 32) + g);
 }
 
 // `now`: a line's value with its `of`-th arrival, as its bringer found it;
@@ -72,16 +72,16 @@ FR_DEVICE void line_full(uint64_t* line, uint64_t now, uint32_t of, Full full) {
 // A word's arrival with `set` bits set, of a call of `words` words: at its
 // group's line, where there is one, and at the first.
 template <class Mem, bool kKept>
-FR_DEVICE void arrive_word(const Arrivals& a, uint64_t w, uint64_t words, uint32_t set) {
+FR_DEVICE void arrive_word(const Arrivals& a, uint32_t w, uint32_t words, uint32_t set) {
   const bool grouped = words > kArriveGroup;
-  const uint64_t g = w / kArriveGroup, left = words - g * kArriveGroup;
+  const uint32_t g = w / kArriveGroup, left = words - g * kArriveGroup;
   uint64_t* const line = grouped ? group_line(a, g) : arrive_line(a, 0);
-  const uint32_t of = uint32_t(left < kArriveGroup ? left : kArriveGroup);
+  const uint32_t of = left < kArriveGroup ? left : kArriveGroup;
   const uint64_t add = (uint64_t(set) << 32) + 1, now = Mem::add(line, add) + add;
   if (uint32_t(now) != of) return;
   line_full<Mem, kKept>(line, now, of, [&](uint32_t count) {
     if (grouped) {
-      const uint32_t groups = uint32_t((words + kArriveGroup - 1) / kArriveGroup);
+      const uint32_t groups = (words + kArriveGroup - 1) / kArriveGroup;
       const uint64_t one = (uint64_t(count) << 32) + 1, all = Mem::add(arrive_line(a, 0), one) + one;
       if (uint32_t(all) == groups)
         line_full<Mem, kKept>(arrive_line(a, 0), all, groups, [&](uint32_t c) { *a.count = c; });
@@ -103,22 +103,24 @@ FR_DEVICE void arrive_chunks(const Arrivals& a, uint64_t n, const uint64_t (&c)[
     now[k] = 0;
     if (!on[k]) continue;
     const uint64_t add = (uint64_t(bit[k]) << (32 + (c[k] & 31))) + 1;
-    now[k] = Mem::add(arrive_line(a, 1 + (c[k] >> 5)), add) + add;
+    now[k] = Mem::add(arrive_line(a, 1 + uint32_t(c[k] >> 5)), add) + add;
   }
-  auto here = [&](uint64_t w) { return uint32_t(n - 32 * w < 32 ? n - 32 * w : 32); };
+  const uint32_t words = uint32_t((n + 31) / 32), last = uint32_t(n - 1) % 32 + 1;
+  auto here = [&](uint32_t w) { return w + 1 == words ? last : 32u; };
   for (;;) {  // one copy of what follows a full word, whichever of the chunks filled it
-    uint64_t w = 0, full = 0;
+    uint32_t w = 0;
+    uint64_t full = 0;
 #pragma unroll
     for (int k = 0; k < N; k++)
-      if (!full && uint32_t(now[k]) == here(c[k] >> 5)) {
-        w = c[k] >> 5;
+      if (!full && uint32_t(now[k]) == here(uint32_t(c[k] >> 5))) {
+        w = uint32_t(c[k] >> 5);
         full = now[k];
         now[k] = 0;
       }
     if (!full) return;
     line_full<Mem, kKept>(arrive_line(a, 1 + w), full, here(w), [&](uint32_t bits) {
       a.bitmap[w] = bits;
-      arrive_word<Mem, kKept>(a, w, (n + 31) / 32, uint32_t(__builtin_popcount(bits)));
+      arrive_word<Mem, kKept>(a, w, words, uint32_t(__builtin_popcount(bits)));
     });
     if (N == 1) return;
   }

@@ -1016,15 +1016,19 @@ __global__ __launch_bounds__(B) void k_pack_chunk(const SrcUnit* __restrict__ un
 
 // What becomes of the bits of an operation by whole chunks.  With lines of
 // arrivals (arrive.h) the kernel writes the bitmap and the count itself.
-// Without (the compare that allocates nothing, states of more than kArriveMost
-// chunks) each chunk leaves a flag for the finalize kernel.
+// Without (the compare that allocates nothing, states and some lists of more
+// than kArriveMost chunks) each chunk leaves a flag for the finalize kernel.
 // Against a finalize launch (us): 48 small tensors restored 21.5 -> 18.7, a
 // state of five 64 KiB chunks unpacked 12.5 -> 9.8, a repair of 20 chunks 42.1
 // -> 39.3.  A workgroup stays until its atomic has returned, which costs where
 // there are many: 4 KiB chunks, 6,300 unpacked 31.7 -> 31.3 and compared 44.8
-// -> 45.6 (12,500), 25,000 unpacked 102 -> 106, 188,000 278 -> 295.  Lists, whose
-// length the host does not know, always take it (4,060 of 214,684 chunks of
-// 64 KiB 215.6 -> 216.6, all of 11,800 578 -> 582).
+// -> 45.6 (12,500), 25,000 unpacked 102 -> 106, 188,000 278 -> 295.  A list
+// whose length the host does not know takes it (4,060 of 214,684 chunks of
+// 64 KiB 215.6 -> 216.6): it is usually short.  One of known length does so up
+// to kArriveMost chunks, and in chunks below 32 KiB always (9,000 of 16 KiB
+// 81 -> 79, 100,000 612 -> 610); of 32 KiB and more a CU holds one or two
+// workgroups, and the finalize launch is faster (12,000 of 64 KiB 372 us against
+// 381 by arrivals, 60,000 1,467 against 1,525; 60,000 of 32 KiB 757 against 776).
 constexpr uint32_t kArriveMost = 8192;
 struct Finish {
   Arrivals arrive;  // lines NULL: flags
@@ -1234,7 +1238,7 @@ template <int B>
 __global__ __launch_bounds__(B) void k_unpack_list_chunk(
     const PlainUnit* __restrict__ plain, const DerivedUnit* __restrict__ derived,
     const u64* __restrict__ counts, uint32_t cvec, const uint8_t* __restrict__ payload, uint8_t* dst,
-    const fr_chunk_sum* __restrict__ sent, const uint32_t* __restrict__ bad,
+    const fr_chunk_sum* __restrict__ sent, const uint32_t* bad /* may be fin.flags */,
     const uint32_t* __restrict__ bits, u64 c0, u64 c1, const u64* __restrict__ pay_of,
     Finish fin) {
   __shared__ u64 lds[2][B / 64][2];
@@ -2243,7 +2247,8 @@ int small_impl(const SmallArgs& m, hipStream_t st) {
     return int(hipGetLastError());
   }
   u64* count = reinterpret_cast<u64*>(m.count);
-  const bool arrive = m.arrive && (m.list_counts || m.n_chunks <= kArriveMost);
+  const bool list_arrives = m.list_counts && (!m.exact || B < 512);
+  const bool arrive = m.arrive && (list_arrives || m.n_chunks <= kArriveMost);
   const Finish fin{Arrivals{arrive ? m.arrive : nullptr, m.bitmap, m.count, m.n_chunks}, m.flags};
   if (m.op == SmallArgs::kUnpack) {
     const dim3 grid(grid_for<B>(u64(m.n_derived) + m.n_plain, m.cfg));

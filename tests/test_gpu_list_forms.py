@@ -57,3 +57,43 @@ def test_list_forms_match_oracle(C, n_bytes, small, monkeypatch):
     for k, ids in enumerate(lists):
         for seg in (None, 4096) if k % 3 == 0 and n < 10000 else (None,):
             _one(t, C, src, recv, ids.astype(np.uint32), rng, f"C={C} list {k} seg={seg}", seg=seg)
+
+
+@pytest.mark.parametrize("C", [1 << 14, 1 << 15, 1 << 16])
+def test_long_host_lists_write_every_bit_and_the_count(C):
+    """Host lists around the length from which lists of large chunks take a
+    finalize launch (8,192; below 32 KiB chunks the last workgroup to arrive
+    writes bits and count at any length): consecutive and scattered ids, none,
+    some and all chunks bad."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2509_03047_amd import flashrestore as F
+
+    rng = np.random.default_rng(C + 1)
+    rows, off = [], 0
+    for n in [C // 4 + 9] + [int(x) for x in rng.integers(1, 9, size=9000)]:  # one entry of two chunks
+        rows.append((off, off, n, W.F32, -1))
+        off += -(-4 * n // 16) * 16
+    t = np.array(rows, dtype=W.TABLE_DTYPE)
+    plan = F.Plan(t, C, off, off)
+    n = plan.n_chunks
+    assert n == 9002
+    src = torch.from_numpy(rng.integers(0, 256, size=off, dtype=np.uint8)).to("cuda")
+    for ids in (np.arange(8192), np.arange(8193), np.arange(3, n), np.delete(np.arange(n), 5)[:8192],
+                np.delete(np.arange(n), [5, 8000])):
+        ids = ids.astype(np.uint32)
+        payload = torch.empty(plan.delta_layout(ids), dtype=torch.uint8, device="cuda")
+        sums = torch.empty(len(ids), 2, dtype=torch.int64, device="cuda")
+        plan.pack_chunks(src, ids, payload, sums)
+        for share in (0.0, 0.2, 1.0):
+            want = np.flatnonzero(rng.random(len(ids)) < share)
+            sent = sums.clone()
+            sent[torch.from_numpy(want).to("cuda"), 1] ^= 2
+            dst = torch.zeros_like(src)
+            bad = torch.full(((len(ids) + 31) // 32,), -1, dtype=torch.int32, device="cuda")
+            n_bad = plan.empty_counter().fill_(-1)
+            plan.unpack_chunks(payload, sent, ids, dst, bad, n_bad)
+            assert int(n_bad.item()) == len(want), (len(ids), share)
+            words = bad.cpu().numpy().view(np.uint32)
+            got = np.flatnonzero(np.unpackbits(words.view(np.uint8), bitorder="little"))  # past the list: clear
+            assert np.array_equal(got, want), (len(ids), share)
