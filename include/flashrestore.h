@@ -213,11 +213,12 @@ typedef struct fr_plan_info {
  * at once.  FLASHRESTORE_ORDER_VERIFY / _CHECKSUM (defaults 1, 0): the
  * compare's or the checksum's slices in arena address order rather than
  * chunk order (they differ for tables that list tensors out of arena
- * order).  Where none of these is set, small states (and some chunk sizes)
- * take one whole chunk per workgroup in an operation instead of its walk and
- * tile; FLASHRESTORE_SMALL gives the largest state, in bytes, that does so in
- * every operation (0: none; chunks up to 64 KiB only) in place of the built-in
- * rule.  FLASHRESTORE_MAX_GRID caps the workgroups per launch (0 or
+ * order).  An operation for which none of these is set takes one whole chunk
+ * per workgroup instead of its walk and tile in small states (and at some
+ * chunk sizes), and so do the delta calls where none is set for pack or
+ * unpack; FLASHRESTORE_SMALL gives the largest state, in bytes, that does so
+ * (0: none; chunks up to 64 KiB only) in place of the built-in rule.
+ * FLASHRESTORE_MAX_GRID caps the workgroups per launch (0 or
  * unset: one per slice or tile). */
 int fr_plan_create(const fr_tensor_desc* table, uint32_t n_entries, uint64_t chunk_bytes,
                    uint64_t src_arena_bytes, uint64_t dst_arena_bytes, fr_plan** out);

@@ -391,12 +391,36 @@ LaunchCfg launch_config() {
   return cfg;
 }
 
+// The operations (kSmall*) for which a variable chooses a tile, a walk, an
+// order or a kind of load, that is one of the kernels that take slices or
+// tiles.  The delta lists take pack's and unpack's.
+uint32_t tuned_ops() {
+  static const char* const kOptions[] = {"TILE", "LINE", "ABSORB", "BUF", "ORDER"};
+  static const struct {
+    const char* suffix;
+    uint32_t ops;
+  } kOps[] = {{"", kSmallAll | kSmallLists},
+              {"_PACK", kSmallPack | kSmallLists},
+              {"_UNPACK", kSmallUnpack | kSmallLists},
+              {"_VERIFY", kSmallVerify | kSmallVerifySums},
+              {"_CHECKSUM", kSmallChecksum}};
+  uint32_t ops = 0;
+  char name[64];
+  for (const char* o : kOptions)
+    for (const auto& op : kOps) {
+      std::snprintf(name, sizeof name, "FLASHRESTORE_%s%s", o, op.suffix);
+      const char* v = std::getenv(name);
+      if (v && *v) ops |= op.ops;
+    }
+  return ops;
+}
+
 // The operations that take one whole chunk per workgroup (kSmall*): those of
 // states small enough that launches and the dependent loads before the data
 // decide, and those whose walks cope badly with the chunk size.  A variable
-// that chooses a tile, a walk, an order or a kind of load turns it off (those
-// choose among the other kernels); FLASHRESTORE_SMALL gives one limit in
-// bytes of state for all operations instead of the rule below.  The lines
+// that chooses an operation's tile, walk, order or kind of load turns it off
+// for that operation (tuned_ops); FLASHRESTORE_SMALL gives one limit in
+// bytes of state for all the others instead of the rule below.  The lines
 // stand where the two change places in a sweep of states of 3 MB to 14 GB, of
 // aligned tensors and of tensors at 16-byte offsets, in chunks of 64 bytes to
 // 64 KiB (us, walk -> whole chunks):
@@ -420,22 +444,14 @@ LaunchCfg launch_config() {
 //             1 KiB chunks 431 -> 372); larger: 276 MB of 64 KiB chunks
 //             44.3 -> 41.4, 1.4 GB of 16 KiB chunks 202 -> 211
 uint32_t small_ops(const fr_plan* p) {
-  static const char* const kOptions[] = {"TILE", "LINE", "ABSORB", "BUF", "ORDER"};
-  static const char* const kOps[] = {"", "_PACK", "_UNPACK", "_VERIFY", "_CHECKSUM"};
-  char name[64];
-  for (const char* o : kOptions)
-    for (const char* op : kOps) {
-      std::snprintf(name, sizeof name, "FLASHRESTORE_%s%s", o, op);
-      const char* v = std::getenv(name);
-      if (v && *v) return 0;
-    }
   const Layout& L = p->layout;
   if (L.longest > kSmallChunk) return 0;
+  const uint32_t free_ops = (kSmallAll | kSmallLists) & ~tuned_ops();
   // what a workgroup holds, and the chunk size unless no chunk is that long
   const uint64_t held = 64 * uint64_t(small_threads(L.longest)), C = std::min(L.C, held);
   const uint64_t state = L.state_bytes, MiB = uint64_t(1) << 20;
   const uint64_t limit = env_u64("FLASHRESTORE_SMALL", ~uint64_t(0));
-  if (limit != ~uint64_t(0)) return state <= limit ? kSmallAll | kSmallLists : 0;
+  if (limit != ~uint64_t(0)) return state <= limit ? free_ops : 0;
   const bool src_lines = p->src_align >= kLine, dst_lines = p->dst_align >= kLine;
   const bool filled = C <= 16384 || 2 * state >= L.n_chunks * held;  // chunks mostly whole
   const uint64_t most = filled ? 64 * MiB : 8 * MiB;
@@ -447,7 +463,7 @@ uint32_t small_ops(const fr_plan* p) {
   if (src_lines ? C == 2048 || (C > 2048 && state <= most) : C >= 256 && ((C <= 32768 && filled) || state <= most))
     ops |= kSmallVerifySums;
   if (C <= 2048 || state <= 320 * MiB) ops |= kSmallChecksum;
-  return ops;
+  return ops & free_ops;
 }
 
 }  // namespace

@@ -609,6 +609,30 @@ def test_walks_follow_the_alignment_of_the_side_written():
                 os.environ[k] = v
 
 
+def test_a_variable_for_one_operation_leaves_the_others_whole_chunks(monkeypatch):
+    """A tile, walk, order or load chosen for one operation takes that
+    operation off whole chunks (plan info: 5), and no other; one chosen for all
+    takes all off; every output equals the oracle's either way."""
+    from paper_2509_03047_amd import flashrestore as F
+
+    for k in [k for k in os.environ if k.startswith("FLASHRESTORE_")]:
+        monkeypatch.delenv(k)
+    rng = np.random.default_rng(78)
+    t, sb, db = W.random_tiny_table(rng, max_entries=9, max_numel=9000)
+    src = W.random_tiny_state(t, sb, rng)
+    for name, value, walks in ((None, None, (5, 5)), ("TILE_PACK", "4", (0, 5)), ("BUF_PACK", "1", (0, 5)),
+                               ("ABSORB_UNPACK", "0", (5, 0)), ("TILE_VERIFY", "7", (5, 5)),
+                               ("ORDER_CHECKSUM", "1", (5, 5)), ("LINE_UNPACK", "1", (5, 0)), ("TILE", "5", (0, 0))):
+        if name:
+            monkeypatch.setenv("FLASHRESTORE_" + name, value)
+        plan = F.Plan(t, 4096, sb, db)
+        got = (plan.info["pack_walk"], plan.info["unpack_walk"])
+        assert tuple(5 if g == 5 else 0 for g in got) == walks, (name, got)
+        _check_against_oracle(t, 4096, src, sb, db, corrupt_rng=rng, tag=f"{name}")
+        if name:
+            monkeypatch.delenv("FLASHRESTORE_" + name)
+
+
 def test_mixed_tiles_per_operation():
     """Each operation with its own tile (so one plan holds several walks of
     different slice sizes) still gives the oracle's bytes."""
