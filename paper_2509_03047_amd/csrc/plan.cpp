@@ -460,7 +460,11 @@ uint32_t small_ops(const fr_plan* p) {
   if (C >= 2048 && state <= (C <= 4096 && !dst_lines ? 1024 * MiB : most)) ops |= kSmallUnpack;
   if (C >= 2048 && state <= most) ops |= kSmallVerify;
   if (C >= 256 && C <= 4096 && !src_lines) ops |= kSmallVerify;
-  if (src_lines ? C == 2048 || (C > 2048 && state <= most) : C >= 256 && ((C <= 32768 && filled) || state <= most))
+  // aligned chunks of several of the compare's slices of 1 KiB or less (2 KiB
+  // chunks by default): summed slice by slice, each with a reduction of its own
+  const uint32_t slice = slice_bytes(L.C, p->cfg.tile_verify);
+  const bool short_slices = slice <= 1024 && C > slice;
+  if (src_lines ? short_slices || (C > 2048 && state <= most) : C >= 256 && ((C <= 32768 && filled) || state <= most))
     ops |= kSmallVerifySums;
   if (C <= 2048 || state <= 320 * MiB) ops |= kSmallChecksum;
   return ops & free_ops;
