@@ -1,8 +1,10 @@
 """Randomised GPU parity campaign: random tables (1-200 entries, scattered
-layouts, derived parameters), each under a random launch configuration
-(one tile for all, or tiles chosen by chunk size, sometimes one operation
-with its own, the pack / unpack / compare / checksum walks, absorbing last slices,
-buffer loads, walk orders, grid and delta grid caps) and a random payload
+layouts, derived parameters), each under a random launch configuration (in
+half of them one tile for all, or tiles chosen by chunk size, sometimes one
+operation with its own, the pack / unpack / compare / checksum walks, absorbing
+last slices, buffer loads, walk orders; in the other half none of these, so
+that operations take whole chunks by the built-in rule, or all or none by
+FLASHRESTORE_SMALL; always grid and delta grid caps) and a random payload
 segment alignment, chunks of 16 B to 1 MiB, random wire corruption; whole
 restore, replica compare, checksum and (at 16-byte segments) a delta repair
 of random chunks, every output against the oracle bit for bit.  Results
@@ -29,24 +31,29 @@ KNOBS = ("FLASHRESTORE_TILE", "FLASHRESTORE_LINE_PACK", "FLASHRESTORE_LINE_UNPAC
          "FLASHRESTORE_BUF_VERIFY", "FLASHRESTORE_BUF_CHECKSUM", "FLASHRESTORE_ORDER_VERIFY",
          "FLASHRESTORE_ORDER_CHECKSUM", "FLASHRESTORE_MAX_GRID", "FLASHRESTORE_DELTA_GRID",
          "FLASHRESTORE_LINE", "FLASHRESTORE_TILE_PACK", "FLASHRESTORE_TILE_UNPACK",
-         "FLASHRESTORE_TILE_VERIFY", "FLASHRESTORE_TILE_CHECKSUM")
+         "FLASHRESTORE_TILE_VERIFY", "FLASHRESTORE_TILE_CHECKSUM", "FLASHRESTORE_SMALL")
 
 
 def _random_knobs(rng) -> str:
     for k in KNOBS:
         os.environ.pop(k, None)
-    tile = int(rng.integers(-4, 11))  # negative: unset, each tile chosen by the chunk size
-    if tile >= 0:
-        os.environ["FLASHRESTORE_TILE"] = str(tile)
-    if rng.random() < 0.25:  # one operation with a tile of its own
-        os.environ[str(rng.choice(KNOBS[16:]))] = str(int(rng.integers(0, 11)))
-    for k in ("FLASHRESTORE_LINE_PACK", "FLASHRESTORE_LINE_UNPACK"):
-        v = int(rng.integers(-1, 5))  # -1: unset, the walk chosen by the table
-        if v >= 0:
-            os.environ[k] = str(v)
-    for k in KNOBS[3:13]:
-        if rng.random() < 0.5:
-            os.environ[k] = str(int(rng.integers(0, 2)))
+    if rng.random() < 0.5:  # whole chunks by rule, everywhere or nowhere
+        small = str(rng.choice(["", "", "0", str(1 << 40), str(1 << 40)]))
+        if small:
+            os.environ["FLASHRESTORE_SMALL"] = small
+    else:
+        tile = int(rng.integers(-4, 11))  # negative: unset, each tile chosen by the chunk size
+        if tile >= 0:
+            os.environ["FLASHRESTORE_TILE"] = str(tile)
+        if rng.random() < 0.25:  # one operation with a tile of its own
+            os.environ[str(rng.choice(KNOBS[16:20]))] = str(int(rng.integers(0, 11)))
+        for k in ("FLASHRESTORE_LINE_PACK", "FLASHRESTORE_LINE_UNPACK"):
+            v = int(rng.integers(-1, 5))  # -1: unset, the walk chosen by the table
+            if v >= 0:
+                os.environ[k] = str(v)
+        for k in KNOBS[3:13]:
+            if rng.random() < 0.5:
+                os.environ[k] = str(int(rng.integers(0, 2)))
     os.environ["FLASHRESTORE_MAX_GRID"] = str(int(rng.choice([0, 0, 0, 1, 7, 300])))
     os.environ["FLASHRESTORE_DELTA_GRID"] = str(int(rng.choice([65536, 65536, 1, 13])))
     return " ".join(f"{k[13:]}={os.environ[k]}" for k in KNOBS if k in os.environ)

@@ -1,14 +1,18 @@
-"""Chunk sums folded from the partial sums that the main kernels store: every
-number of slices a chunk can have in the folds' ranges (one, up to 8, 16 and
-more slices per whole chunk), one slice more or less, tiles that begin with
-other chunks, and small and large chunk counts, against the CPU oracle (all
-outputs bit for bit, with a corrupted wire)."""
+"""Chunk sums folded from the partial sums that the main kernels store (whole
+chunks, which fold nothing, are switched off): every number of slices a chunk
+can have in the folds' ranges (one, up to 8, 16 and more slices per whole
+chunk), one slice more or less, and tiles that begin with other chunks, against
+the CPU oracle (all outputs bit for bit, with a corrupted wire).  The folds of
+more than 16,384 chunks of many slices run in the full-size tests."""
+import os
+
 import numpy as np
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
+from paper_2509_03047_amd import flashrestore as F  # noqa: E402
 from paper_2509_03047_amd import workloads as W  # noqa: E402
 from tests.test_gpu_parity_small import _check_against_oracle  # noqa: E402
 
@@ -33,10 +37,15 @@ def _table(C, rng, align):
 
 @pytest.mark.parametrize("align", [16, 128])
 @pytest.mark.parametrize("C", [16, 1 << 12, 1 << 13, 1 << 14, 1 << 15, 1 << 16, 1 << 17, 1 << 18, 1 << 20])
-def test_partial_sums_fold_to_the_oracle(C, align):
+def test_partial_sums_fold_to_the_oracle(C, align, monkeypatch):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
+    for k in [k for k in os.environ if k.startswith("FLASHRESTORE_")]:
+        monkeypatch.delenv(k)
+    monkeypatch.setenv("FLASHRESTORE_SMALL", "0")
     rng = np.random.default_rng(C + align)
     t, sb, db = _table(C, rng, align)
     src = W.random_tiny_state(t, sb, rng)
+    info = F.Plan(t, C, sb, db).info
+    assert 5 not in (info["pack_walk"], info["unpack_walk"])
     _check_against_oracle(t, C, src, sb, db, corrupt_rng=rng, tag=f"fold C={C} align={align}")
