@@ -691,6 +691,11 @@ __global__ __launch_bounds__(B) void k_unpack(const DerivedUnit* __restrict__ de
 struct UnpackBlocksArgs {
   u64 n_units, n_blocks, stride;
 };
+// Tiles of up to two vectors a thread ask for 8 waves per SIMD: left alone, the
+// compiler takes 102 scalar registers at two vectors, which leaves 7 (unpack of
+// tensors at 16-byte offsets, us: 2.4 GB in 8 KiB chunks 800 -> 775, in 4 KiB
+// 860 -> 806; at one vector, for chunks up to 1 KiB, 78 registers instead of 90:
+// in 1 KiB chunks 1,300 -> 1,167).
 
 // One unit's part of a receiver tile: the unit's vectors from du on are the
 // tile's vectors from lb on.  Its ragged tail (if in the tile) is masked to
@@ -708,7 +713,7 @@ __device__ __forceinline__ void unpack_tile_tail(const PlainUnit& r, uint32_t lb
 }
 
 template <int B, int U>
-__global__ __launch_bounds__(B) void k_unpack_blocks(UnpackBlocksArgs a,
+__global__ __launch_bounds__(B, U <= 2 ? 8 : 1) void k_unpack_blocks(UnpackBlocksArgs a,
                                                      const PlainUnit* __restrict__ units,
                                                      const u64* __restrict__ blocks,
                                                      const uint8_t* __restrict__ payload,
