@@ -471,8 +471,10 @@ DeltaBuild delta_build(const fr_plan* plan, const ChunkList& list, uint64_t* use
   return b;
 }
 
-// The launch configuration of a pack over a list: a list whose length the
-// host knows needs no cap on its workgroups.
+// The launch configuration of a pack over a list by slices: a list whose length
+// the host knows needs no cap on its workgroups.  (Unpack keeps the cap: its
+// walk has slots for the whole list twice over, sent and parameter chunks, of
+// which at least half are idle: 1,028 chunks of 256 KiB 151 us without, 131 with.)
 LaunchCfg list_config(const fr_plan* plan, const ChunkList& list) {
   LaunchCfg cfg = plan->cfg;
   if (list.exact) cfg.delta_grid = 0;
@@ -562,7 +564,7 @@ int unpack_list(const fr_plan* plan, const void* payload, uint64_t payload_bytes
   a.c0 = list.c0;
   a.c1 = list.c1;
   a.pay_of = plan->d_delta_payof;
-  return launch_result(launch_unpack_delta(a, list_config(plan, list), stream));
+  return launch_result(launch_unpack_delta(a, plan->cfg, stream));
 }
 
 }  // namespace
