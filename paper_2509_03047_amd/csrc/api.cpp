@@ -513,9 +513,10 @@ int unpack_list(const fr_plan* plan, const void* payload, uint64_t payload_bytes
                 const fr_chunk_sum* sums, const ChunkList& list, void* dst_base, uint32_t* bad_bitmap,
                 uint64_t* n_bad, hipStream_t stream) {
   const uint64_t bound = list.bound;
-  const bool whole = bound && plan->cfg.small & kSmallLists;
+  const bool whole = bound && plan->cfg.small & kSmallLists && !(list.exact && list_slices(plan->layout.C, bound));
   if (bound) {
     DeltaBuild b = delta_build(plan, list, nullptr, payload_bytes, plan->cfg.tile_unpack, n_bad);
+    if (!whole) b.acc = plan->scratch.acc;
     b.arrive = whole ? plan->d_list_arrive : nullptr;
     b.arrive_n = bound;
     FR_TRY(launch_result(launch_delta_build(b, false, stream)));

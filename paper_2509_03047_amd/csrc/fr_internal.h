@@ -197,6 +197,14 @@ constexpr uint32_t kSmallPack = 1, kSmallUnpack = 2, kSmallVerify = 4, kSmallVer
                    kSmallChecksum = 16, kSmallAll = 31;
 constexpr uint32_t kSmallLists = 32;  // the delta calls' listed chunks
 
+// Long lists of small chunks are unpacked by slices also where lists take whole
+// chunks: a workgroup of 64 threads holds 4 KiB, and the capped grid of the
+// slices goes on to its next chunk with no atomic to wait for.  Of 370 MB (us,
+// whole chunks / slices): 117,016 chunks of 64 bytes 311 / 273, 73,136 of 256
+// bytes 139 / 132, 329,122 of 1 KiB 522 / 509; shorter lists 22,000 of 256 bytes
+// 65 / 69, 43,700 of 1 KiB 84 / 86.
+inline bool list_slices(uint64_t C, uint64_t n_ids) { return C <= 1024 && n_ids > 256 * C; }
+
 // Device scratch owned by a plan: partial sums, one place per slot of the
 // longest walk (the delta calls use the same memory as G accumulators per
 // chunk, see accumulators_per_chunk), a second set for the replica compare's

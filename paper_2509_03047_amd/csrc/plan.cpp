@@ -842,7 +842,7 @@ int build_unpack_walk(fr_plan* p, const std::vector<ChunkRec>& recs,
 int build_scratch(fr_plan* p, const Staging& st) {
   const Layout& L = p->layout;
   uint64_t g = 0;
-  if (!(p->cfg.small & kSmallLists))
+  if (!(p->cfg.small & kSmallLists) || list_slices(L.C, L.n_chunks))
     for (int t : {p->cfg.tile_pack, p->cfg.tile_unpack})
       g = std::max<uint64_t>(g, accumulators_per_chunk(L.C, t));
   auto bytes = [](uint64_t places) { return (places * sizeof(fr_chunk_sum) + 255) & ~uint64_t(255); };

@@ -52,6 +52,9 @@ def test_list_forms_match_oracle(C, n_bytes, small, monkeypatch):
     lists.append(np.unique(rng.integers(0, n, size=max(1, n // 3))))         # dense
     lists.append(np.unique(rng.integers(0, n, size=min(n, 40))))             # scattered
     lists.append(np.unique(np.concatenate([first[:-1], first[1:] - 1])))     # ends of entries
+    for k in (256 * C, 256 * C + 1):  # longer lists of small chunks are unpacked by slices
+        if k + 7 <= n:
+            lists += [np.arange(k) + 7, np.delete(np.arange(n), 9)[:k]]
     if n > 2:
         lists.append(np.delete(np.arange(n), n // 2))                        # all but one
     for k, ids in enumerate(lists):
