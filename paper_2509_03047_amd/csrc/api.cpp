@@ -324,6 +324,7 @@ extern "C" int fr_verify_replicas_noalloc(const fr_plan* plan, const void* base_
   scr.acc_b = reinterpret_cast<fr_chunk_sum*>(p + flag_bytes + acc_bytes);
   SlotTable t = *walk;
   t.parts = nullptr;  // accumulators per chunk: the array has no room for a place per slot
+  t.in_order = false;
   return launch_result(launch_verify(plan->d_units, t, uint32_t(L.n_chunks), L.C, base_a,
                                      base_b, diff_bitmap, n_diff, sums_a, sums_b, scr, plan->cfg,
                                      stream));

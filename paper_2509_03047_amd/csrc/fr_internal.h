@@ -136,6 +136,9 @@ struct SlotTable {
   // Per chunk id, where its partial sums lie (NULL: the operation adds into
   // per-chunk accumulators, or every chunk has one slot and is summed whole).
   const ChunkParts* parts = nullptr;
+  // Every chunk has one slot, in chunk order: chunk c's sum lies at slot c's
+  // place, and nothing (parts) says so.
+  bool in_order = false;
   uint64_t part0 = 0;  // the walk's first place in the partial sums (behind a tile walk's)
 };
 

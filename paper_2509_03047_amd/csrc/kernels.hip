@@ -1342,7 +1342,8 @@ struct FinalArgs {
   uint32_t n_chunks;  // bitmap bits written (ceil(n_chunks / 32) words)
   uint32_t g_shift;
   const u64* live;    // NULL, or a device count: positions from *live on are not chunks (bit 0, no sums)
-  const ChunkParts* parts;  // NULL: accumulators
+  const ChunkParts* parts;  // NULL: accumulators, or with in_order chunk c's one place is slot c's
+  bool in_order;
   u64 part0, stride;        // of the slot walk the places belong to
   u64 tile_stride;          // of the tile walk
 };
@@ -1353,7 +1354,8 @@ template <int kLanes, int kBatch>
 __device__ __forceinline__ fr_chunk_sum fold(const FinalArgs& f, const fr_chunk_sum* acc, u64 c,
                                              uint32_t sub) {
   u64 s = 0, ws = 0;
-  if (!f.parts) {  // kLanes = 1
+  if (f.in_order) return acc[f.part0 + slot_place(c, f.stride)];  // kLanes = 1, as below
+  if (!f.parts) {
     const u64 first = c << f.g_shift;
     for (u64 i = first; i < first + (u64(1) << f.g_shift); i++) {
       s += acc[i].sum;
@@ -1928,7 +1930,7 @@ inline Walk walk_for(uint64_t C, uint32_t tile_bytes, const SlotTable& t) {
   w.line = t.shift;
   w.absorb = t.absorb;
   w.count = reinterpret_cast<const u64*>(t.count);
-  w.out = t.parts ? kOutParts : kOutAtomic;
+  w.out = t.parts || t.in_order ? kOutParts : kOutAtomic;
   w.part0 = t.part0;
   w.spc_shift = sh;
   w.g_shift = sh > kAccSlicesShift ? sh - kAccSlicesShift : 0;
@@ -1938,6 +1940,7 @@ inline Walk walk_for(uint64_t C, uint32_t tile_bytes, const SlotTable& t) {
 // The partial sums of a walk as the finalize kernel's input.
 inline void fold_parts(FinalArgs& f, const Walk& wk, const SlotTable& t) {
   f.parts = t.parts;
+  f.in_order = t.in_order;
   f.part0 = wk.part0;
   f.stride = wk.stride;
 }
@@ -1997,7 +2000,7 @@ int pack_impl(bool store, const SrcUnit* units, const SlotTable& slots, uint32_t
   if (n_chunks == 0) return 0;
   Walk wk = walk_for(C, B * U * 16, slots);
   // one slot per chunk: the sums of a slice are the chunk's
-  const bool whole = !wk.count && !slots.parts && wk.n_slices == n_chunks;
+  const bool whole = !wk.count && wk.out == kOutAtomic && wk.n_slices == n_chunks;
   if (whole) wk.out = kOutWhole;
   fr_chunk_sum* acc = whole ? sums : scr.acc;
   const auto* s = static_cast<const uint8_t*>(src);
@@ -2174,7 +2177,7 @@ int verify_impl(const SrcUnit* units, const SlotTable& slots, uint32_t n_chunks,
                 const LaunchCfg& cfg, hipStream_t st) {
   Walk wk = walk_for(C, B * U * 16, slots);
   // one slot per chunk: the sums of a slice are the chunk's
-  const bool whole = sums_a && !slots.parts && wk.n_slices == n_chunks;
+  const bool whole = sums_a && wk.out == kOutAtomic && wk.n_slices == n_chunks;
   if (whole) wk.out = kOutWhole;
   const u64 n_acc = u64(n_chunks) << wk.g_shift;
   fr_chunk_sum* acc_a = whole ? sums_a : scr.acc;

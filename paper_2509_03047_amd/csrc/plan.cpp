@@ -628,7 +628,7 @@ int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st) 
     for (const auto& w : p->src_walks) {
       if (w.sl != sl || w.t.shift != shift || w.t.absorb != absorb || w.arena_order != arena) continue;
       have = true;
-      if (w.parts && compare && sums) need_places(p, w.t, 0, true);
+      if ((w.parts || w.t.in_order) && compare && sums) need_places(p, w.t, 0, true);
     }
     if (have) continue;
     if (arena && by_addr.empty()) {  // entries by sender offset, each entry's chunks in order
@@ -656,10 +656,12 @@ int build_src_walks(fr_plan* p, const std::vector<SrcUnit>& units, Staging& st) 
     w.arena_order = arena;
     // with one slot per chunk a slice's sums are the chunk's: a small state
     // needs no partial sums; nor does a walk that only compares bytes
-    if (sums && (b.n() != L.n_chunks || L.n_chunks > kWholeChunks)) take_parts(w, L, st);
+    const bool single = b.n() == L.n_chunks;
+    w.t.in_order = sums && single && !arena && L.n_chunks > kWholeChunks;
+    if (sums && !w.t.in_order && (!single || L.n_chunks > kWholeChunks)) take_parts(w, L, st);
     const int rc = upload_walk(b, w, st, w.parts);
     if (rc != FR_OK) return rc;
-    if (w.parts) need_places(p, w.t, 0, compare);
+    if (w.parts || w.t.in_order) need_places(p, w.t, 0, compare);
   }
   return FR_OK;
 }

@@ -49,3 +49,23 @@ def test_partial_sums_fold_to_the_oracle(C, align, monkeypatch):
     info = F.Plan(t, C, sb, db).info
     assert 5 not in (info["pack_walk"], info["unpack_walk"])
     _check_against_oracle(t, C, src, sb, db, corrupt_rng=rng, tag=f"fold C={C} align={align}")
+
+
+@pytest.mark.parametrize("swap", [False, True])
+@pytest.mark.parametrize("n", [32768, 32769, 33000])
+def test_sums_of_chunks_of_one_slice(n, swap, monkeypatch):
+    """Chunks of one slice each: stored as they are up to 32,768 of them, above
+    that at the slots' places, found by the chunk's id where the slots are in
+    chunk order and through the table of places where they are not (the compare
+    of a table that lists its tensors out of arena order)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    for k in [k for k in os.environ if k.startswith("FLASHRESTORE_")]:
+        monkeypatch.delenv(k)
+    monkeypatch.setenv("FLASHRESTORE_SMALL", "0")
+    C, rng = 256, np.random.default_rng(n)
+    a, b = n // 3, n - n // 3  # chunks of the two entries, the last one ragged
+    off = (0, a * C) if not swap else (b * C, 0)
+    t = np.array([(off[0], 0, a * C // 4, W.F32, -1), (off[1], a * C, b * C // 4 - 3, W.F32, -1)], dtype=W.TABLE_DTYPE)
+    src = W.random_tiny_state(t, n * C, rng)
+    _check_against_oracle(t, C, src, n * C, n * C, corrupt_rng=rng, tag=f"n={n} swap={swap}")
