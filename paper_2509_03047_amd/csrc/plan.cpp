@@ -424,12 +424,20 @@ uint32_t tuned_ops() {
 // stand where the two change places in a sweep of states of 3 MB to 14 GB, of
 // aligned tensors and of tensors at 16-byte offsets, in chunks of 64 bytes to
 // 64 KiB (us, walk -> whole chunks):
-//   pack      1 KiB and more: 44 MB of 64 KiB chunks 20.0 -> 15.8, 276 MB
-//             84.6 -> 80.1, but 4 GB of 16 KiB chunks 1,171 -> 1,255; smaller
+//   pack      2 and 4 KiB at any size, and 1 KiB where payload segments start
+//             inside lines (3.9 GB of 1 KiB chunks 1,690 -> 1,604, of 2 KiB 1,340
+//             -> 1,219, of 4 KiB 1,235 -> 1,213; with segments on lines 2 GB of
+//             2 KiB 693 -> 653, but of 1 KiB 818 -> 848); otherwise small states: 44 MB of 64
+//             KiB chunks 20.0 -> 15.8, 276 MB 84.6 -> 80.1, but 4 GB of 16 KiB
+//             chunks 1,171 -> 1,255; 32 KiB chunks, whose 512 threads fill a CU
+//             least evenly, turn earlier (279 MB 91.9 -> 89.5, 503 MB 157.7 ->
+//             162.7, 400 MB of tensors of all sizes 132.3 -> 138.1); smaller
 //             chunks gain only in the smallest states (3 MB of 64-byte chunks
 //             59 -> 18; 121 MB of 256-byte chunks 155 -> 180)
 //   unpack    44 MB 19.7 -> 18.3, 276 MB 86.0 -> 89.2; at 16-byte offsets
-//             chunks of 2 and 4 KiB gain longer (770 MB 295 -> 279) and
+//             chunks of 4 KiB gain longer (782 MB 256 -> 252, 1.0 GB 342 -> 338,
+//             2.4 GB 806 -> 817) and so do those of 2 KiB up to about 128 MB
+//             (112 MB 46.4 -> 40.5; 252 MB 91.9 -> 97.8, 722 MB 250 -> 272), and
 //             64 KiB chunks that are mostly short lose (37 MB 19.7 -> 22.6);
 //             256-byte chunks 61 -> 73
 //   compare   like unpack (44 MB 17.6 -> 16.0, 238 MB 71.4 -> 73.2); at 16-byte
@@ -456,8 +464,11 @@ uint32_t small_ops(const fr_plan* p) {
   const bool filled = C <= 16384 || 2 * state >= L.n_chunks * held;  // chunks mostly whole
   const uint64_t most = filled ? 64 * MiB : 8 * MiB;
   uint32_t ops = kSmallLists;
-  if (state <= (C >= 1024 && filled ? 512 : 8) * MiB) ops |= kSmallPack;
-  if (C >= 2048 && state <= (C <= 4096 && !dst_lines ? 1024 * MiB : most)) ops |= kSmallUnpack;
+  const uint64_t most_pack = (C < 1024 || !filled ? 8 : C == 32768 ? 320 : 512) * MiB;
+  const bool pack_any = C <= 4096 && C >= (p->pay_align < kLine ? 1024 : 2048);
+  if (pack_any || state <= most_pack) ops |= kSmallPack;
+  const uint64_t most_unpack = dst_lines || C > 4096 ? most : (C == 4096 ? 1024 : 128) * MiB;
+  if (C >= 2048 && state <= most_unpack) ops |= kSmallUnpack;
   if (C >= 2048 && state <= most) ops |= kSmallVerify;
   if (C >= 256 && C <= 4096 && !src_lines) ops |= kSmallVerify;
   // aligned chunks of several of the compare's slices of 1 KiB or less (2 KiB

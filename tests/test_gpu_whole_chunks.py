@@ -51,3 +51,26 @@ def test_states_around_the_size_rule_match_oracle():
         nb = -(-4 * n // 16) * 16
         src = W.random_tiny_state(t, nb, rng)
         _check_against_oracle(t, 1 << 16, src, nb, nb, corrupt_rng=rng, tag=f"64 MiB {extra:+d}")
+
+
+@pytest.mark.parametrize("C,mb,align,seg,pack,unpack", [
+    (4096, 2000, 16, 16, True, False), (4096, 900, 16, 16, True, True), (4096, 900, 256, 16, True, False),
+    (2048, 2000, 16, 4096, True, False), (2048, 120, 16, 16, True, True), (2048, 200, 16, 16, True, False),
+    (1024, 600, 16, 16, True, False), (1024, 600, 16, 4096, False, False), (1024, 500, 16, 4096, True, False),
+    (1 << 15, 300, 256, 16, True, False), (1 << 15, 400, 256, 16, False, False), (1 << 14, 400, 256, 16, True, False),
+    (1 << 16, 60, 256, 16, True, True), (1 << 16, 80, 256, 16, True, False), (1 << 16, 600, 256, 16, False, False),
+])
+def test_which_states_take_whole_chunks(C, mb, align, seg, pack, unpack, monkeypatch):
+    """The sizes at which pack and unpack change from whole chunks to walks, by
+    chunk size and alignment of the side written (plan info: 5 is whole
+    chunks).  Plans only: no state is built."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2509_03047_amd import flashrestore as F
+
+    monkeypatch.delenv("FLASHRESTORE_SMALL", raising=False)
+    per = (mb * 1_000_000 // 4 // 16 // 4096 * 4096) + (4 if align == 16 else 0)  # four entries
+    step = 16 * per + (0 if align == 16 else -16 * per % align)
+    t = np.array([(k * step, k * step, 4 * per, W.F32, -1) for k in range(4)], dtype=W.TABLE_DTYPE)
+    info = F.Plan(t, C, 4 * step, 4 * step, segment_align=seg).info
+    assert ((info["pack_walk"] == 5), (info["unpack_walk"] == 5)) == (pack, unpack), info
