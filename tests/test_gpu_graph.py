@@ -345,14 +345,14 @@ def test_two_plans_delta_calls_on_two_streams(small, monkeypatch):
         assert torch.equal(b["bad"], r["bad"]) and torch.equal(b["nbad"], r["nbad"])
 
 
-def test_compare_sums_of_one_plan_on_several_streams():
+@pytest.mark.parametrize("n", [8000, 40_000])  # one workgroup and several of the finalize kernel
+def test_compare_sums_of_one_plan_on_several_streams(n):
     """fr_compare_sums uses nothing of the plan but its sizes: calls of one
     plan queued on four streams without ordering between them, beside whole
     restores of the same plan on a fifth, each give their own bits and count
     (and so does every later call)."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    n = 40_000  # 40 workgroups of the finalize kernel
     t = np.array([(0, 0, 4 * n, W.F32, -1)], dtype=W.TABLE_DTYPE)
     plan = F.Plan(t, 16, 16 * n, 16 * n)
     rng = np.random.default_rng(44)
