@@ -212,8 +212,9 @@ inline bool list_slices(uint64_t C, uint64_t n_ids) { return C <= 1024 && n_ids 
 // longest walk (the delta calls use the same memory as G accumulators per
 // chunk, see accumulators_per_chunk), a second set for the replica compare's
 // sums of arena B and unpack's parameter images, and one 32-bit flag per
-// chunk.  Every operation writes or clears what it reads, so what an earlier
-// one left does not matter; operations on one plan must not overlap in time.
+// chunk.  Every operation writes or clears what it reads here, so what an earlier
+// one left does not matter (the lines of arrivals, which are elsewhere, come back
+// to zero by themselves: arrive.h); operations on one plan must not overlap in time.
 struct Scratch {
   fr_chunk_sum* acc = nullptr;
   fr_chunk_sum* acc_b = nullptr;

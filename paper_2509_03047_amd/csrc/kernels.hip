@@ -22,12 +22,12 @@
 //     beside those of the XCD's neighbouring slices: a line that two XCDs
 //     write costs more than the store (a checksum of 16 KiB chunks that
 //     stored each chunk's sums in chunk order ran 7 % slower);
-//   * lists built on the device and the compare that allocates nothing add
-//     into 64-bit accumulators with atomics instead (order-independent, hence
-//     deterministic).  Atomics on one address serialise, so no accumulator
-//     takes more than 16 slices (32 for a bf16 parameter fed by master
-//     slices): a chunk of SPC slices owns G = max(1, SPC / 16) of them,
-//     cleared first;
+//   * lists of large chunks (and long ones of tiny chunks) and the compare
+//     that allocates nothing add into 64-bit accumulators with atomics
+//     instead (order-independent, hence deterministic).  Atomics on one
+//     address serialise, so no accumulator takes more than 16 slices (32 for
+//     a bf16 parameter fed by master slices): a chunk of SPC slices owns
+//     G = max(1, SPC / 16) of them, cleared first;
 //   * replica compare marks a differing chunk with a plain store of 1 to a
 //     per-chunk flag (idempotent, so no atomics on shared bitmap words);
 //   * for tensors that start inside a cache line, pack and unpack walk
@@ -264,14 +264,15 @@ struct Walk {
 
 // Where a slice's sums go.  Whole-state operations store them at the slice's
 // own place, 16 bytes next to those of the XCD's neighbouring slots, for the
-// finalize kernel to fold; that needs no cleared memory, and the two 64-bit
-// atomics per slice it replaces (32 bytes of HBM writes each) cost unpack of
-// the 8B share 1.7 % (4,104 -> 4,035 us in the kernel), the checksum of
-// 16 KiB chunks 5 % (1,151 -> 1,093 us) and that of 1 MiB chunks 1.3 %.  A
-// walk with one slice per chunk stores the chunk's sums themselves.  Lists
-// built on the device (whose longest form would need a place for every
-// slice of every chunk's full length) and the compare that allocates
-// nothing add into cleared accumulators.
+// finalize kernel to fold; that needs no cleared memory, and without the two
+// 64-bit atomics per slice it replaces (32 bytes of HBM writes each) the
+// kernels' profiled averages fell by 4 % for the checksum of 16 KiB chunks
+// (1,152 -> 1,106 us), 3 % of 64 KiB (1,997 -> 1,939) and 1 % of 1 MiB chunks
+// (4,505 -> 4,456), and for unpack of the 8B share by 0.6 % (4,130 -> 4,104,
+// no more than processes differ).  A walk with one slice per chunk stores the
+// chunk's sums themselves in states of few chunks.  Lists that go by slices
+// (whose longest form would need a place for every slice of every chunk's full
+// length) and the compare that allocates nothing add into cleared accumulators.
 enum SumOut { kOutAtomic = 0, kOutParts = 1, kOutWhole = 2 };
 
 // Workgroup ids a launch covers: every slot of the walk, or for a list
@@ -960,8 +961,11 @@ __global__ __launch_bounds__(B) void k_verify(const SrcUnit* __restrict__ units,
 // (unpack: one derived group or plain chunk): it reads the chunk's record,
 // then everything of the chunk at once, every load in flight together
 // through buffer resources, and ends up with the chunk's whole sums.  Pack
-// and the checksum are then one launch, and unpack and the compare leave one
-// flag per chunk to the finalize kernel.  B threads hold kSmallVecs vectors
+// and the checksum are then one launch, and so are unpack and the compare up to
+// kArriveMost chunks (Finish; above that they leave one flag per chunk to the
+// finalize kernel).  At 1,024 threads the registers that hold the chunk leave
+// room for one workgroup per CU (but for the checksum and the compare without
+// sums).  B threads hold kSmallVecs vectors
 // each, B * 64 >= the plan's longest chunk (threads for C bytes instead, where
 // 64 KiB chunks hold at most 12 KB: 3,160 of them packed in 32 us, by slices in
 // 21).
